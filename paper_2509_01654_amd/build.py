@@ -25,20 +25,19 @@ DEVICE_FLAGS = [
 ]
 
 
-def _la_splits():
+def _ranges(macro):
     text = open(os.path.join(CSRC, "nw_kernels.h"), encoding="utf-8").read()
-    m = re.search(r"#define NW_LA_SPLITS (.*)", text)
-    return [(int(a), int(b)) for a, b in re.findall(r"X\((\d+), (\d+)\)", m.group(1))]
-
-
-def _class8():
-    text = open(os.path.join(CSRC, "nw_kernels.h"), encoding="utf-8").read()
-    m = re.search(r"#define NW_CLASS8 (.*)", text)
+    m = re.search(r"#define " + macro + r" (.*)", text)
     return [(int(a), int(b)) for a, b in re.findall(r"X\((\d+), (\d+)\)", m.group(1))]
 
 
 def _units():
-    units = [
+    # the longest compilations first
+    units = []
+    for lo, hi in reversed(_ranges("NW_BITS_SPLITS")):
+        units.append((f"k_bits_inst_{lo}_{hi}", os.path.join(CSRC, "k_bits_inst.hip"),
+                      [f"-DNW_BITS_LO={lo}", f"-DNW_BITS_HI={hi}"]))
+    units += [
         ("nw_api", os.path.join(CSRC, "nw_api.cpp"), []),
         ("nw_server", os.path.join(CSRC, "nw_server.cpp"), []),
         ("nw_batch", os.path.join(CSRC, "nw_batch.cpp"), []),
@@ -48,10 +47,10 @@ def _units():
         ("k_launch", os.path.join(CSRC, "k_launch.hip"), []),
         ("nw_noalloc", os.path.join(CSRC, "nw_noalloc.hip"), []),
     ]
-    for lo, hi in _la_splits():
+    for lo, hi in _ranges("NW_LA_SPLITS"):
         units.append((f"k_inst_{lo}_{hi}", os.path.join(CSRC, "k_inst.hip"),
                       [f"-DNW_LA_LO={lo}", f"-DNW_LA_HI={hi}"]))
-    for lo, hi in _class8():
+    for lo, hi in _ranges("NW_CLASS8"):
         units.append((f"k_batch_inst_{lo}_{hi}", os.path.join(CSRC, "k_batch_inst.hip"),
                       [f"-DNW_CLASS_LO={lo}", f"-DNW_CLASS_HI={hi}"]))
     return units

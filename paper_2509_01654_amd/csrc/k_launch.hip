@@ -15,6 +15,7 @@
 #include "k_probe.h"
 #include "k_query.h"
 #include "k_topk.h"
+#include "k_topk_bits.h"
 #include "k_topk_code.h"
 #include "k_tri_code.h"
 #include "k_tri_tiled.h"
@@ -82,6 +83,9 @@ const KernelTables &kernel_tables()
     static bool init = [] {
 #define X(lo, hi) nw_fill_##lo(t);
         NW_LA_SPLITS
+#undef X
+#define X(lo, hi) nw_fill_bits_##lo(t);
+        NW_BITS_SPLITS
 #undef X
 #define X(lo, hi) nw_fill_class_##lo(t);
         NW_CLASS8
@@ -440,7 +444,67 @@ hipError_t launch_merge(const uint64_t *partial, int P, int kin, int64_t rows, i
     return hipGetLastError();
 }
 
-hipError_t launch_topk_main(const DevVocab &V, const TopkArgs &T, hipStream_t stream)
+__global__ __launch_bounds__(256) void k_column_layout(const uint8_t *bsym, const uint8_t *blen, int WB, int64_t ndw,
+                                                       uint32_t *ccol)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= ndw) return;
+    const int lane = (int)(t & 63);
+    const int64_t gq = t >> 6, g = gq / kColDwords;
+    const int q = (int)(gq % kColDwords);
+    const int lb = blen[g * 64 + lane], front = (int)blen[g * 64 + 63] - lb;
+    const uint8_t *w = bsym + (g * 64 + lane) * WB;
+    uint32_t x = 0;
+    for (int k = 0; k < 4; ++k) {
+        const int i = 4 * q + k - front;
+        if (i >= 0 && i < lb) x |= (uint32_t)w[i] << (8 * k);
+    }
+    ccol[t] = x;
+}
+
+hipError_t launch_column_layout(const DevVocab &V, uint32_t *ccol, hipStream_t stream)
+{
+    const int64_t ndw = (int64_t)V.nb * V.CB * kColDwords;
+    if (ndw == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((ndw + 255) / 256)), dim3(256), 0, stream, V.bsym, V.blen, V.WB,
+                       ndw, ccol);
+    return hipGetLastError();
+}
+
+// NW_DP=packed keeps the packed binary16 kernels where the bit-plane kernels
+// would apply (both are exact; for comparisons).
+static bool packed_dp_only()
+{
+    static const bool only = [] {
+        const char *e = std::getenv("NW_DP");
+        return e && std::strcmp(e, "packed") == 0;
+    }();
+    return only;
+}
+
+// Parts the 64-word column steps of a tile are dealt to: a launch of few tiles
+// (each one workgroup per row length) halves them until it has 384, or four
+// steps, one per wavefront, are left.  20k words (210 tiles): main pass
+// 0.53 -> 0.35 ms; 30k words with a matrix (465 tiles, larger tables to
+// build): 3.7 ms whole, 4.0 ms in three parts.
+static int col_splits(uint64_t tiles, int CB)
+{
+    int s = 1;
+    while (tiles * s < 384 && 2 * s <= CB / 256) s *= 2;
+    return s;
+}
+
+// The main pass takes the bit-plane kernels where the scoring fits them and
+// the histogram copies fit beside one group of row words.
+static bool topk_bits_applies(const DevVocab &V, const TopkArgs &T)
+{
+    if (V.bits == 0 || packed_dp_only()) return false;
+    const int tab = V.bits == 2 ? Bits2::kTab : Bits3::kTab, wm = V.bits == 2 ? Bits2::kWmax : Bits3::kWmax;
+    return (T.hist == nullptr || T.nbins <= kBitMaxBins) && T.lo <= V.lo &&
+           topk_bits_lds_bytes(V.lmax, tab, wm, V, T.nbins, T.hist != nullptr) <= kMaxLdsBytes;
+}
+
+hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream)
 {
     if (V.n < 2) return hipSuccess;
     const uint32_t nblk_pairs = (uint32_t)((uint64_t)V.nb * (V.nb + 1) / 2);
@@ -448,6 +512,27 @@ hipError_t launch_topk_main(const DevVocab &V, const TopkArgs &T, hipStream_t st
     StreamFork fork(stream);
     hipError_t ef = fork.begin();
     if (ef != hipSuccess) return ef;
+    const bool bits = topk_bits_applies(V, T);
+    if (bits) {
+        const int h = T.hist != nullptr;
+        const int width = V.bits == 2 ? Bits2::kTab : Bits3::kTab, wm = V.bits == 2 ? Bits2::kWmax : Bits3::kWmax;
+        for (int c = 0; c < kBitClasses && bit_class_lo(c) <= V.lmax; ++c) {
+            const int lo = bit_class_lo(c), hi = std::min(bit_class_hi(c), (int)V.lmax);
+            uint32_t any = 0;
+            for (int LA = lo; LA <= hi; ++LA) any += h_maxrg[LA];
+            if (any == 0) continue;
+            DevVocab Vc = V;
+            TopkArgs Tc = T;
+            Tc.bit_lds = topk_bits_lds_bytes(hi, width, wm, V, T.nbins, h);
+            Tc.col_splits = col_splits((uint64_t)nblk_pairs * (T.phase_hi - T.phase_lo + 1) / T.phase_mod, V.CB);
+            void *args[] = {&Vc, &Tc};
+            hipError_t e = launch_dyn(tab.topk_bits[V.bits - 2][h][c],
+                                      dim3(nblk_pairs * (uint32_t)Tc.col_splits, (uint32_t)(hi - lo + 1)), Tc.bit_lds,
+                                      fork, args);
+            if (e != hipSuccess) return e;
+        }
+        return fork.end();
+    }
     for (int LA = 0; LA <= V.lmax; ++LA) {
         DevVocab Vc = V;
         TopkArgs Tc = T;

@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -84,7 +85,7 @@ constexpr int kPhasePeriod = 8;
 // Byte offsets of every region inside d_mem.
 struct Layout {
     uint64_t csym, clen, bsym, blen, bcol, rpairs, rp_off, dpairs, dp_off, wtab, submat, borig, gpairs, gp_off, psym, plen,
-        porig, prank, total;
+        porig, prank, rg_off, ccol, wplanes, total;
     int CB, WB, nb;
     uint64_t nprobe, pslots;
 };
@@ -123,6 +124,11 @@ Layout make_layout(uint64_t n, uint32_t max_len)
     L.plen = take(L.pslots);
     L.porig = take(L.pslots * 4);
     L.prank = take(L.pslots * 2);
+    // the bit-plane kernels' arrays (words of at most kMaxLen symbols)
+    const bool narrow = max_len <= (uint32_t)kMaxLen;
+    L.rg_off = take(narrow ? ((uint64_t)L.nb * (max_len + 1) + 1) * 4 : 0);
+    L.wplanes = take(narrow ? 256 * 3 * 8 * 4 : 0);
+    L.ccol = take(narrow ? slots * kWordBytes : 0);   // last: written on the device
     L.total = o;
     return L;
 }
@@ -377,6 +383,17 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     const long hi = (long)max_len * std::max((long)smax, 0L);
     if (lo < -32768 || hi > 32767) return fail(NW_ERANGE, "score bounds [%ld, %ld] leave int16", lo, hi);
 
+    // planes of a difference in the bit-plane kernels (nw_bits.h): 2 when every
+    // match weighs 3 and every mismatch 1, 3 when no weight exceeds 7; 0 (the
+    // packed kernels) past that, and for words the register rows do not take
+    int bits = 0;
+    if (max_len <= (uint32_t)kMaxLen && symmetric && wmax <= 7 && sc->gap >= -7) {
+        bool plain = sc->gap >= -3;
+        for (int x = 0; x < A && plain; ++x)
+            for (int y = 0; y < A && plain; ++y) plain = sim[(size_t)x * A + y] - 2 * sc->gap == (x == y ? 3 : 1);
+        bits = plain ? 2 : 3;
+    }
+
     const Layout L = make_layout(n, max_len);
     if (!d_mem) return fail(NW_EINVAL, "d_mem is NULL");
     if ((uintptr_t)d_mem % 256) return fail(NW_EINVAL, "d_mem must be 256-byte aligned");
@@ -386,7 +403,9 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     if (int rc = refuse_capture((hipStream_t)hip_stream, "nw_load_vocab")) return rc;
 
     // host image of the device layout
-    std::vector<uint8_t> img(L.total, 0);
+    const bool narrow = max_len <= (uint32_t)kMaxLen;
+    const uint64_t img_bytes = narrow ? L.ccol : L.total;
+    std::vector<uint8_t> img(img_bytes, 0);
     // lane words are padded with the sentinel symbol (= alphabet)
     std::memset(img.data() + L.bsym, A, (size_t)L.nb * L.CB * L.WB);
     std::memset(img.data() + L.psym, A, (size_t)L.pslots * L.WB);
@@ -512,6 +531,29 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
             ++s;
         }
     }
+    // groups of 32 slots by their longest word (the last: slots are length-sorted)
+    std::vector<uint32_t> h_maxrg(LM + 1, 0);
+    if (narrow) {
+        uint32_t *rg_off = reinterpret_cast<uint32_t *>(img.data() + L.rg_off);
+        const uint32_t per = (uint32_t)L.CB / 32;
+        for (int blk = 0; blk < L.nb; ++blk) {
+            uint32_t g = (uint32_t)blk * per;
+            for (int l = 0; l <= LM; ++l) {
+                const uint32_t from = g;
+                rg_off[(size_t)blk * (LM + 1) + l] = from;
+                while (g < (uint32_t)(blk + 1) * per && blen[(size_t)g * 32 + 31] == l) ++g;
+                h_maxrg[l] = std::max(h_maxrg[l], g - from);
+            }
+        }
+        rg_off[(size_t)L.nb * (LM + 1)] = (uint32_t)L.nb * per;
+        uint32_t *wplanes = reinterpret_cast<uint32_t *>(img.data() + L.wplanes);
+        for (int x = 0; x < A; ++x)
+            for (int y = 0; y < A; ++y) {
+                const int w = std::min(std::max(sim[(size_t)x * A + y] - 2 * sc->gap, 0), 7);
+                for (int q = 0; q < 3; ++q)
+                    if (w >> q & 1) wplanes[((size_t)x * 3 + q) * 8 + y / 32] |= 1u << (y % 32);
+            }
+    }
     for (int x = 0; x < A; ++x)
         for (int y = 0; y < A; ++y) {
             wtab[(size_t)x * A + y] = f16_bits_of_int(sim[(size_t)x * A + y] - 2 * sc->gap);
@@ -519,12 +561,11 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         }
 
     hipStream_t st = (hipStream_t)hip_stream;
-    hipError_t e = hipMemcpyAsync(d_mem, img.data(), L.total, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return dev_fail(e, "copying the dictionary");
-    e = hipStreamSynchronize(st);
+    hipError_t e = hipMemcpyAsync(d_mem, img.data(), img_bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return dev_fail(e, "copying the dictionary");
 
-    nw_vocab *v = new nw_vocab();
+    std::unique_ptr<nw_vocab> owner(new nw_vocab());
+    nw_vocab *v = owner.get();
     uint8_t *base = static_cast<uint8_t *>(d_mem);
     DevVocab &D = v->dev;
     D.csym = base + L.csym;
@@ -559,10 +600,18 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     D.nprobe = (int32_t)L.nprobe;
     D.lo = (int32_t)lo;
     D.hi = (int32_t)hi;
+    D.bits = bits;
+    D.rg_off = reinterpret_cast<const uint32_t *>(base + L.rg_off);
+    D.wplanes = reinterpret_cast<const uint32_t *>(base + L.wplanes);
+    D.ccol = reinterpret_cast<const uint32_t *>(base + L.ccol);
+    e = narrow ? launch_column_layout(D, reinterpret_cast<uint32_t *>(base + L.ccol), st) : hipSuccess;
+    const hipError_t es = hipStreamSynchronize(st);   // the copy reads img: wait in any case
+    if (e != hipSuccess || es != hipSuccess) return dev_fail(e != hipSuccess ? e : es, "copying the dictionary");
     v->h_gp_off = h_gp_off;
     v->h_csym.assign(csym, csym + n * L.WB);
     v->h_clen.assign(clen, clen + n);
     v->h_rp_off.assign(rp_off, rp_off + (size_t)L.nb * (LM + 1) + 1);
+    v->h_maxrg = h_maxrg;
     v->h_maxrp.assign(LM + 1, 0);
     for (uint64_t r = 0; r < L.nb; ++r)
         for (uint32_t la = 0; la <= LM; ++la) {
@@ -584,7 +633,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     v->d_mem = d_mem;
     hipGetDevice(&v->device);
     v->d_bytes = d_bytes;
-    *out = v;
+    *out = owner.release();
     return ok();
 }
 
@@ -775,12 +824,12 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
     T.phase_mod = kPhasePeriod;
     T.phase_lo = 0;
     T.phase_hi = 0;
-    if ((e = launch_topk_main(D, T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    if ((e = launch_topk_main(D, v->h_maxrg.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
     if ((e = launch_tighten(cnt, lists, W.cap, (int64_t)n, (int)k, thr, st)) != hipSuccess)
         return dev_fail(e, "launching the threshold update");
     T.phase_lo = 1;
     T.phase_hi = kPhasePeriod - 1;
-    if ((e = launch_topk_main(D, T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    if ((e = launch_topk_main(D, v->h_maxrg.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
     if ((e = hipEventRecord(vm->ev[2], st)) != hipSuccess) return dev_fail(e, "recording a timing event");
     // 3. the best k of each word's candidates
     if ((e = launch_select(cnt, lists, W.cap, (int64_t)n, (int)k, D.lo, d_score, d_index, ovf, reinterpret_cast<int32_t *>(ovf + 1), st)) != hipSuccess)

@@ -75,6 +75,16 @@ struct DevVocab {
     int64_t pslots;
     int32_t nprobe;
     int32_t lo, hi;             // score bounds
+    // Bit-plane kernels (nw_bits.h).  bits: 0 when the scoring or a word is
+    // outside what they hold, else the planes of a difference (2 or 3).
+    // Groups of 32 consecutive slots, numbered over the dictionary: those of
+    // block r whose longest word has L symbols are rg_off[r*(LMAX+1)+L] ..
+    // rg_off[r*(LMAX+1)+L+1].  ccol: the words of each 64 consecutive slots
+    // as the lanes read them.  wplanes[x][q][c/32]: bit q of max(w(x, c), 0).
+    int32_t bits;
+    const uint32_t *rg_off;     // [nb*(LMAX+1)+1]
+    const uint32_t *ccol;       // [nb*CB/64][12][64]
+    const uint32_t *wplanes;    // [256][3][8]
 };
 
 enum OutKind { OUT_I8 = 1, OUT_I16 = 2, OUT_EDGES = 3 };
@@ -95,6 +105,9 @@ struct EdgeSink {
     int32_t normalised;
     int32_t lo, hi, den;
 };
+
+// Write the ccol array of a loaded dictionary (from bsym and blen).
+hipError_t launch_column_layout(const DevVocab &V, uint32_t *ccol, hipStream_t stream);
 
 // Launchers.  Each enqueues on `stream` and returns the hipError_t of the
 // launches.  Launchers with one launch per row length (or class) spread those
@@ -164,8 +177,9 @@ hipError_t launch_scatter_lists(const int16_t *qs, const int32_t *qi, const int3
 
 // Main pass of the all-pairs top-k: candidates >= thr into per-word lists,
 // plus the histogram.
+// h_maxrg[LA] (host) = most groups of 32 row words with longest length LA in one block.
 struct TopkArgs;
-hipError_t launch_topk_main(const DevVocab &V, const TopkArgs &T, hipStream_t stream);
+hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream);
 
 // Zero n counters (a kernel, so graph capture records no memset node).
 hipError_t launch_reset_counters(uint32_t *counters, int n, hipStream_t stream);

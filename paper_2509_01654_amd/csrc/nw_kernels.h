@@ -13,6 +13,9 @@ namespace nw {
 #define NW_CLASS8 X(0, 7) X(8, 15) X(16, 23) X(24, 31) X(32, 39) X(40, 47) X(48, 48)
 constexpr int kNumClass8 = 7;
 
+// Classes of four lengths of the bit-plane kernels, by translation unit.
+#define NW_BITS_SPLITS X(0, 1) X(2, 3) X(4, 4) X(5, 5) X(6, 6) X(7, 7) X(8, 8) X(9, 9) X(10, 10) X(11, 11)
+
 struct KernelTables {
     const void *tri[kMaxLen + 1];
     const void *tri_code1[kMaxLen + 1];  // the same with score codes and dword stores, one row pair a step
@@ -21,6 +24,7 @@ struct KernelTables {
     const void *probe_thr[kMaxLen + 1];  // threshold pre-pass by selection
     const void *topk[kMaxLen + 1];
     const void *topk_code[kMaxLen + 1];  // the same with the score-code epilogue
+    const void *topk_bits[2][2][kMaxLen / 4];   // bit planes, classes of 4 lengths: [Bits2, Bits3][without, with histogram]
     const void *edges[kMaxLen + 1];      // threshold edge emitter
     const void *persist1[kMaxLen + 1];   // persistent batched kernel, one per row length
     const void *persist8[kNumClass8];    // persistent batched kernel, one per class of 8 lengths
@@ -29,6 +33,9 @@ struct KernelTables {
 
 #define X(lo, hi) void nw_fill_##lo(KernelTables &t);
 NW_LA_SPLITS
+#undef X
+#define X(lo, hi) void nw_fill_bits_##lo(KernelTables &t);
+NW_BITS_SPLITS
 #undef X
 #define X(lo, hi) void nw_fill_class_##lo(KernelTables &t);
 NW_CLASS8

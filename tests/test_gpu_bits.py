@@ -1,0 +1,107 @@
+"""GPU parity of the bit-plane kernels against the oracle (bit-exact).
+
+The sizes are the edges of their layout: words of every length up to the
+register-row limit of 48 (each length has its own code, most groups of 32 row
+words mix lengths), empty words, dictionaries that leave padding slots and
+half-filled groups, alphabets on both sides of a 32-symbol mask, and scorings on
+both sides of every rule that picks 2 planes, 3 planes or the packed kernels.
+Scores are integers: no tolerance.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from synth import uniform_vocab, vocab_from_words, zipf_vocab
+
+pytestmark = pytest.mark.gpu
+
+
+def _nw():
+    import torch
+    import paper_2509_01654_amd as nw
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return nw, torch
+
+
+def _matrix(alphabet, lo, hi, diag, seed=9):
+    rng = np.random.default_rng(seed)
+    m = np.triu(rng.integers(lo, hi + 1, size=(alphabet, alphabet)), 1)
+    m = m + m.T
+    np.fill_diagonal(m, diag)
+    return m
+
+
+# name: (alphabet, similarity matrix as scored by the oracle, gap, Scoring keywords)
+def _scorings():
+    out = {}
+    for name, A, match, mismatch, gap in [
+        ("plain", 40, 1, -1, -1),             # 2 planes
+        ("plain_gap2", 33, -1, -3, -2),       # 2 planes, other bounds
+        ("plain_gap0", 6, 3, 1, 0),           # 2 planes, no fill of short rows
+        ("levenshtein", 32, 0, -1, -1),       # 3 planes, weights 2 and 1
+        ("lcs", 3, 1, 0, 0),                  # 3 planes, weights 1 and 0, heavy ties
+        ("negative_weights", 20, 2, -9, -2),  # 3 planes, mismatches weigh -5
+        ("weight_8", 20, 4, -1, -2),          # packed kernels
+    ]:
+        out[name] = (A, oracle.sim_matrix(A, match, mismatch), gap, dict(match=match, mismatch=mismatch))
+    for name, A, lo, hi, diag, gap in [("matrix_64", 64, -3, 3, 3, -2), ("matrix_65", 65, -2, 1, 3, -2),
+                                       ("matrix_200", 200, -1, 0, 1, -1)]:
+        m = _matrix(A, lo, hi, diag)
+        out[name] = (A, m, gap, dict(submat=m))
+    m = oracle.sim_matrix(40, 1, -1)
+    out["plain_as_matrix"] = (40, m, -1, dict(submat=m))
+    return out
+
+
+SCORINGS = _scorings()
+
+
+def _words(n, alphabet, lmax, seed=5):
+    """n words of lengths 0 .. lmax, every length present, some words repeated."""
+    rng = np.random.default_rng(seed)
+    lengths = rng.integers(0, lmax + 1, size=n)
+    lengths[: min(n, lmax + 1)] = np.arange(lmax + 1)[: min(n, lmax + 1)]
+    words = [rng.integers(0, alphabet, size=l) for l in rng.permutation(lengths)]
+    for i in range(0, n - 7, 50):
+        words[i + 6] = words[i]
+    return vocab_from_words(words, alphabet)
+
+
+def _load(name, v):
+    nw, torch = _nw()
+    A, sim, gap, kw = SCORINGS[name]
+    return nw.Vocab(v.symbols, v.offsets, nw.Scoring(alphabet=A, gap=gap, **kw), device="cuda:0"), sim, gap
+
+
+@pytest.mark.parametrize("hist", [True, False])
+@pytest.mark.parametrize("name", list(SCORINGS))
+@pytest.mark.parametrize("n,lmax", [(333, 48), (257, 11)])
+def test_topk_bits(name, n, lmax, hist):
+    _, torch = _nw()
+    v = _words(n, SCORINGS[name][0], lmax)
+    dv, sim, gap = _load(name, v)
+    k = 9
+    sc, ix, h = dv.all_pairs_topk(k, hist=hist)
+    torch.cuda.synchronize()
+    ws, wi, wh = oracle.topk_rows(v.symbols, v.offsets, sim, gap, k, hist_range=dv.bounds)
+    assert np.array_equal(sc.cpu().numpy().astype(np.int32), ws)
+    assert np.array_equal(ix.cpu().numpy(), wi)
+    if hist:
+        assert np.array_equal(h.cpu().numpy().astype(np.uint64), wh)
+
+
+@pytest.mark.parametrize("n", [2, 31, 33, 64, 65, 256, 17000])
+def test_topk_bits_group_edges(n):
+    """Groups and steps that end inside a block, and past the small-block rule."""
+    _, torch = _nw()
+    v = zipf_vocab(n, seed=n, mean_len=6.0, min_len=0, max_len=14)
+    dv, sim, gap = _load("plain", v)
+    sc, ix, h = dv.all_pairs_topk(5)
+    torch.cuda.synchronize()
+    for r0 in {0, max(0, n - 60), (n // 2) & ~31}:
+        r1 = min(n, r0 + 60)
+        ws, wi, _ = oracle.topk_rows(v.symbols, v.offsets, sim, gap, 5, r0=r0, r1=r1)
+        assert np.array_equal(sc.cpu().numpy()[r0:r1].astype(np.int32), ws)
+        assert np.array_equal(ix.cpu().numpy()[r0:r1], wi)
+    assert int(h.sum()) == n * (n - 1) // 2
