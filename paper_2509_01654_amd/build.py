@@ -37,6 +37,9 @@ def _units():
     for lo, hi in reversed(_ranges("NW_BITS_SPLITS")):
         units.append((f"k_bits_inst_{lo}_{hi}", os.path.join(CSRC, "k_bits_inst.hip"),
                       [f"-DNW_BITS_LO={lo}", f"-DNW_BITS_HI={hi}"]))
+    for variant, rng in _ranges("NW_TRI_BITS"):
+        units.append((f"k_tri_bits_inst_{variant}_{rng}", os.path.join(CSRC, "k_tri_bits_inst.hip"),
+                      [f"-DNW_VARIANT={variant}", f"-DNW_RANGE={rng}"]))
     units += [
         ("nw_api", os.path.join(CSRC, "nw_api.cpp"), []),
         ("nw_server", os.path.join(CSRC, "nw_server.cpp"), []),

@@ -1,4 +1,4 @@
-// k_bits_inst.hip -- instantiates the bit-plane kernels for the classes of
+// k_bits_inst.hip -- instantiates the bit-plane top-k kernels for the classes of
 // row lengths NW_BITS_LO .. NW_BITS_HI, a few per translation unit so they
 // build in parallel.  Exports them through nw_fill_bits_<NW_BITS_LO>.
 #include <utility>

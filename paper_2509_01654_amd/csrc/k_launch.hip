@@ -17,6 +17,7 @@
 #include "k_topk.h"
 #include "k_topk_bits.h"
 #include "k_topk_code.h"
+#include "k_tri_bits.h"
 #include "k_tri_code.h"
 #include "k_tri_tiled.h"
 #include "nw_fork.h"
@@ -83,6 +84,9 @@ const KernelTables &kernel_tables()
     static bool init = [] {
 #define X(lo, hi) nw_fill_##lo(t);
         NW_LA_SPLITS
+#undef X
+#define X(v, r) nw_fill_tri_bits_##v##_##r(t);
+        NW_TRI_BITS
 #undef X
 #define X(lo, hi) nw_fill_bits_##lo(t);
         NW_BITS_SPLITS
@@ -161,6 +165,107 @@ static bool plain_epilogue_only()
     return only;
 }
 
+// NW_DP=packed keeps the packed binary16 kernels where the bit-plane kernels
+// would apply (both are exact; for comparisons).
+static bool packed_dp_only()
+{
+    static const bool only = [] {
+        const char *e = std::getenv("NW_DP");
+        return e && std::strcmp(e, "packed") == 0;
+    }();
+    return only;
+}
+
+// The scalar parameters of a dictionary's bit-plane scheme.
+static int bit_tab(const DevVocab &V) { return V.bits == 2 ? Bits2::kTab : Bits3::kTab; }
+static int bit_wmax(const DevVocab &V) { return V.bits == 2 ? Bits2::kWmax : Bits3::kWmax; }
+
+// Scores (not edges) of dictionaries the bit planes hold, where the staging
+// and one group of the longest row words fit in LDS.  16-bit staging covers
+// every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
+bool triangle_bits_applies(const DevVocab &V, int out_kind)
+{
+    if (V.bits == 0 || out_kind == OUT_EDGES || packed_dp_only()) return false;
+    const bool w16 = tri_bits_wide(V);
+    if (w16 && V.bits == 2) return false;
+    return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16) <= kMaxLdsBytes;
+}
+
+// The launches of a bit-plane triangle over the lengths present in h_maxrp:
+// ranges of row lengths (tri_bits_span), the longest rows first.
+struct LengthRange {
+    int lo, hi, range;
+};
+static std::vector<LengthRange> triangle_bits_launches(const DevVocab &V, const uint32_t *h_maxrp)
+{
+    std::vector<LengthRange> out;
+    const int span = V.bits == 2 ? tri_bits_span<Bits2>() : tri_bits_span<Bits3>();
+    for (int r = (V.lmax - 1) / span; r >= 0; --r) {
+        int lo = r == 0 ? 0 : r * span + 1, hi = std::min((r + 1) * span, (int)V.lmax);
+        while (lo <= hi && h_maxrp[lo] == 0) ++lo;
+        while (lo <= hi && h_maxrp[hi] == 0) --hi;
+        if (lo <= hi) out.push_back({lo, hi, r});
+    }
+    return out;
+}
+
+static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
+                                       int out_kind, void *d_out, StreamFork &fork)
+{
+    const KernelTables &tab = kernel_tables();
+    const bool w16 = tri_bits_wide(V);
+    const int scheme = w16 ? 4 : 2 * (V.bits - 2) + (out_kind == OUT_I8 ? 0 : 1);
+    uint32_t rb0 = (uint32_t)(row_of_index(V.n, idx_begin) / V.CB);
+    const uint32_t nr = (uint32_t)(row_of_index(V.n, idx_end - 1) / V.CB) - rb0 + 1;
+    // A workgroup takes one chunk of row groups (blockIdx.z) against nw
+    // windows, its tables serving all of them: as many as leave kWorkgroups
+    // workgroups.
+    auto parts = [&](const LengthRange &L) {
+        const uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16);
+        uint32_t most = 1;
+        for (int LA = L.lo; LA <= L.hi; ++LA) {
+            // rows of longest length LA: those of that length, and up to a
+            // group's worth of shorter ones at either end
+            const uint32_t groups = h_maxrp[LA] * 2 / kBitRows + 2;
+            const uint32_t kg = (uint32_t)tri_bits_groups(LA, bit_tab(V), V.alphabet, V.TW, V.CB, w16, lds);
+            if (h_maxrp[LA]) most = std::max(most, (groups + kg - 1) / kg);
+        }
+        return most;
+    };
+    constexpr uint64_t kWorkgroups = 8192;
+    const std::vector<LengthRange> launches = triangle_bits_launches(V, h_maxrp);
+    uint64_t chunks = 0;
+    for (const LengthRange &L : launches) chunks += (uint64_t)parts(L) * (uint64_t)(L.hi - L.lo + 1);
+    int nw = (int)std::max<uint64_t>(1, std::min<uint64_t>(8, chunks * nr * V.nwin / 2 / kWorkgroups));
+    uint32_t nset = ((uint32_t)V.nwin + nw - 1) / nw;
+    for (const LengthRange &L : launches) {
+        DevVocab Vc = V;
+        uint64_t ib = idx_begin, ie = idx_end;
+        void *po = d_out;
+        uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16);
+        int hi = L.hi;
+        void *args[] = {&Vc, &ib, &ie, &po, &rb0, &nset, &nw, &hi, &lds};
+        hipError_t e = launch_dyn(tab.tri_bits[scheme][L.range],
+                                  dim3(nr * nset, (uint32_t)(L.hi - L.lo + 1), parts(L)), lds, fork, args);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind)
+{
+    if (V.n < 2) return 0;
+    if (triangle_bits_applies(V, out_kind)) return (uint32_t)triangle_bits_launches(V, h_maxrp).size();
+    const int per = V.n <= kClassLaunchMaxWords ? 8 : 1;
+    uint32_t launches = 0;
+    for (int lo = 0; lo <= V.lmax; lo += per) {
+        uint32_t rows = 0;
+        for (int LA = lo; LA <= std::min(lo + per - 1, (int)V.lmax); ++LA) rows += h_maxrp[LA];
+        launches += rows > 0;
+    }
+    return launches;
+}
+
 hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
                                  int out_kind, void *d_out, hipStream_t stream, const EdgeSink *E, StreamFork *shared)
 {
@@ -173,6 +278,11 @@ hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uin
         if (ef != hipSuccess) return ef;
     }
     StreamFork &fork = shared ? *shared : own;
+    if (triangle_bits_applies(V, out_kind)) {
+        const hipError_t e = launch_triangle_bits(V, h_maxrp, idx_begin, idx_end, out_kind, d_out, fork);
+        if (e != hipSuccess) return e;
+        return shared ? hipSuccess : own.end();
+    }
     if (V.n <= kClassLaunchMaxWords) {
         // small dictionaries: one launch per class of 8 row lengths
         // (k_tri_class; the per-length launches would be bound by launch cost)
@@ -444,16 +554,18 @@ hipError_t launch_merge(const uint64_t *partial, int P, int kin, int64_t rows, i
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_column_layout(const uint8_t *bsym, const uint8_t *blen, int WB, int64_t ndw,
-                                                       uint32_t *ccol)
+__global__ __launch_bounds__(256) void k_column_layout(const uint8_t *csym, const uint8_t *len, const uint16_t *col,
+                                                       int window, int WB, int64_t ndw, uint32_t *ccol)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= ndw) return;
     const int lane = (int)(t & 63);
     const int64_t gq = t >> 6, g = gq / kColDwords;
     const int q = (int)(gq % kColDwords);
-    const int lb = blen[g * 64 + lane], front = (int)blen[g * 64 + 63] - lb;
-    const uint8_t *w = bsym + (g * 64 + lane) * WB;
+    const int64_t slot = g * 64 + lane;
+    const int lb = len[slot], front = (int)len[g * 64 + 63] - lb;
+    // padding slots have length 0 and read nothing
+    const uint8_t *w = csym + (slot / window * window + (lb ? (int)col[slot] : 0)) * WB;
     uint32_t x = 0;
     for (int k = 0; k < 4; ++k) {
         const int i = 4 * q + k - front;
@@ -462,24 +574,14 @@ __global__ __launch_bounds__(256) void k_column_layout(const uint8_t *bsym, cons
     ccol[t] = x;
 }
 
-hipError_t launch_column_layout(const DevVocab &V, uint32_t *ccol, hipStream_t stream)
+hipError_t launch_column_layout(const DevVocab &V, const uint8_t *len, const uint16_t *col, int window, int64_t nslots,
+                                uint32_t *ccol, hipStream_t stream)
 {
-    const int64_t ndw = (int64_t)V.nb * V.CB * kColDwords;
+    const int64_t ndw = nslots * kColDwords;
     if (ndw == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((ndw + 255) / 256)), dim3(256), 0, stream, V.bsym, V.blen, V.WB,
-                       ndw, ccol);
+    hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((ndw + 255) / 256)), dim3(256), 0, stream, V.csym, len, col,
+                       window, V.WB, ndw, ccol);
     return hipGetLastError();
-}
-
-// NW_DP=packed keeps the packed binary16 kernels where the bit-plane kernels
-// would apply (both are exact; for comparisons).
-static bool packed_dp_only()
-{
-    static const bool only = [] {
-        const char *e = std::getenv("NW_DP");
-        return e && std::strcmp(e, "packed") == 0;
-    }();
-    return only;
 }
 
 // Parts the 64-word column steps of a tile are dealt to: a launch of few tiles
@@ -499,9 +601,8 @@ static int col_splits(uint64_t tiles, int CB)
 static bool topk_bits_applies(const DevVocab &V, const TopkArgs &T)
 {
     if (V.bits == 0 || packed_dp_only()) return false;
-    const int tab = V.bits == 2 ? Bits2::kTab : Bits3::kTab, wm = V.bits == 2 ? Bits2::kWmax : Bits3::kWmax;
     return (T.hist == nullptr || T.nbins <= kBitMaxBins) && T.lo <= V.lo &&
-           topk_bits_lds_bytes(V.lmax, tab, wm, V, T.nbins, T.hist != nullptr) <= kMaxLdsBytes;
+           topk_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, T.nbins, T.hist != nullptr) <= kMaxLdsBytes;
 }
 
 hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream)
@@ -515,7 +616,6 @@ hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const To
     const bool bits = topk_bits_applies(V, T);
     if (bits) {
         const int h = T.hist != nullptr;
-        const int width = V.bits == 2 ? Bits2::kTab : Bits3::kTab, wm = V.bits == 2 ? Bits2::kWmax : Bits3::kWmax;
         for (int c = 0; c < kBitClasses && bit_class_lo(c) <= V.lmax; ++c) {
             const int lo = bit_class_lo(c), hi = std::min(bit_class_hi(c), (int)V.lmax);
             uint32_t any = 0;
@@ -523,7 +623,7 @@ hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const To
             if (any == 0) continue;
             DevVocab Vc = V;
             TopkArgs Tc = T;
-            Tc.bit_lds = topk_bits_lds_bytes(hi, width, wm, V, T.nbins, h);
+            Tc.bit_lds = topk_bits_lds_bytes(hi, bit_tab(V), bit_wmax(V), V, T.nbins, h);
             Tc.col_splits = col_splits((uint64_t)nblk_pairs * (T.phase_hi - T.phase_lo + 1) / T.phase_mod, V.CB);
             void *args[] = {&Vc, &Tc};
             hipError_t e = launch_dyn(tab.topk_bits[V.bits - 2][h][c],

@@ -73,8 +73,10 @@ __host__ __device__ inline int topk_bits_groups(int LA, int tab, int wmax, int a
 // or what one group needs.
 __host__ __device__ inline uint32_t topk_bits_lds_bytes(int LA, int tab, int wmax, const DevVocab &V, int nbins, int has_hist)
 {
-    const uint32_t one = topk_bits_fixed_bytes(nbins, has_hist) + topk_bits_group_bytes(LA, tab, wmax, V.alphabet, V.lmax);
-    return one > kBitTopkLds ? one : kBitTopkLds;
+    const uint32_t fixed = topk_bits_fixed_bytes(nbins, has_hist);
+    const uint32_t per = topk_bits_group_bytes(LA, tab, wmax, V.alphabet, V.lmax);
+    const uint32_t all = fixed + kBitMaxGroups * per;
+    return all <= kBitTopkLds ? all : fixed + per > kBitTopkLds ? fixed + per : kBitTopkLds;
 }
 
 // One block pair's groups of longest length LA against every splits-th column
@@ -98,6 +100,7 @@ __device__ __forceinline__ void topk_bits_tile(const DevVocab &V, const TopkArgs
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int kg = topk_bits_groups(LA, S::kTab, S::kWmax, A, lmax, T.nbins, HIST, T.bit_lds);
+    if (kg < 1) return;   // the launch's LDS holds a group (topk_bits_lds_bytes)
     const uint32_t gstride = topk_bits_group_bytes(LA, S::kTab, S::kWmax, A, lmax);
     const uint32_t thr_at = bit_group_bytes(LA, S::kTab, A);
     const uint32_t lds0 = lds_addr_of(lds);
@@ -113,7 +116,8 @@ __device__ __forceinline__ void topk_bits_tile(const DevVocab &V, const TopkArgs
 
     for (uint32_t gc = gbeg; gc < gend; gc += (uint32_t)kg) {
         const int ng = (int)min((uint32_t)kg, gend - gc);
-        build_groups<LA, S, kThreads>(V, I0, gc, ng, lds, gstride);
+        build_groups<LA, S, kThreads>(V, I0, ng, lds, gstride,
+                                      [&](int g, int q) { return ((int64_t)gc + g) * kBitRows + q; });
         // threshold planes: lanes 0..31 the row words of a group for one
         // length lb, lanes 32..63 for the next
         for (int x = wave; x < ng * ((lmax + 2) / 2); x += kThreads / 64) {
@@ -158,7 +162,7 @@ __device__ __forceinline__ void topk_bits_tile(const DevVocab &V, const TopkArgs
             taken = (uint32_t)__builtin_amdgcn_readfirstlane((int)taken);
             if (taken >= (uint32_t)steps) break;
             const int st = part + (steps - 1 - (int)taken) * T.col_splits;   // longest words first
-            const ColWords W = col_words(V, J0 / 64 + st, lane);
+            const ColWords W = col_words(V.ccol, V.blen, J0 / 64 + st, lane);
             const uint32_t col = V.bcol[J0 + st * 64 + lane];
             const int64_t j = J0 + col;
             // the lane's threshold as a mask per plane
@@ -309,7 +313,8 @@ void k_topk_bits(DevVocab V, TopkArgs T)
     const int part = (int)(blockIdx.x % (uint32_t)T.col_splits);
     const int LA = bit_class_lo(C) + (int)blockIdx.y;
     if (LA > V.lmax) return;
-    bit_class_dispatch<C>(LA, [&](auto la) { topk_bits_tile<decltype(la)::value, S, HIST>(V, T, r, b, part, lds); });
+    bit_length_dispatch<bit_class_lo(C), bit_class_hi(C)>(
+        LA, [&](auto la) { topk_bits_tile<decltype(la)::value, S, HIST>(V, T, r, b, part, lds); });
 }
 
 }  // namespace nw

@@ -75,6 +75,12 @@ int choose_block(uint64_t n, uint32_t max_len)
 }
 
 
+// Column window of the bit-plane triangle: 1024 words stage 32 rows of a byte
+// in 32 KB of LDS, four workgroups per CU (windows of 512 words: the 50k-word
+// triangle took 0.84 ms against 0.81, a narrow chunk of a 200k-word one 0.32
+// against 0.40; before the launches were merged).
+constexpr int kTriWindow = 1024;
+
 // Probe subset of the top-k threshold pre-pass.
 constexpr uint64_t kMaxProbes = 8192;
 uint64_t num_probes(uint64_t n) { return n < kMaxProbes ? n : kMaxProbes; }
@@ -85,7 +91,8 @@ constexpr int kPhasePeriod = 8;
 // Byte offsets of every region inside d_mem.
 struct Layout {
     uint64_t csym, clen, bsym, blen, bcol, rpairs, rp_off, dpairs, dp_off, wtab, submat, borig, gpairs, gp_off, psym, plen,
-        porig, prank, rg_off, ccol, wplanes, total;
+        porig, prank, rg_off, ccol, wplanes, tlen, tcol, tccol, total;
+    int TW, nwin;
     int CB, WB, nb;
     uint64_t nprobe, pslots;
 };
@@ -128,7 +135,15 @@ Layout make_layout(uint64_t n, uint32_t max_len)
     const bool narrow = max_len <= (uint32_t)kMaxLen;
     L.rg_off = take(narrow ? ((uint64_t)L.nb * (max_len + 1) + 1) * 4 : 0);
     L.wplanes = take(narrow ? 256 * 3 * 8 * 4 : 0);
-    L.ccol = take(narrow ? slots * kWordBytes : 0);   // last: written on the device
+    // the triangle's column windows: the blocks themselves up to kTriWindow words
+    L.TW = std::min(L.CB, kTriWindow);
+    L.nwin = (int)((n + L.TW - 1) / L.TW);
+    const bool windows = narrow && L.TW < L.CB;
+    const uint64_t tslots = windows ? (uint64_t)L.nwin * L.TW : 0;
+    L.tlen = take(tslots);
+    L.tcol = take(tslots * 2);
+    L.ccol = take(narrow ? slots * kWordBytes : 0);   // from here on written on the device
+    L.tccol = take(tslots * kWordBytes);
     L.total = o;
     return L;
 }
@@ -546,6 +561,25 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
             }
         }
         rg_off[(size_t)L.nb * (LM + 1)] = (uint32_t)L.nb * per;
+        if (L.TW < L.CB) {
+            // windows: the slots of their block in order, padding first
+            uint8_t *tlen = img.data() + L.tlen;
+            uint16_t *tcol = reinterpret_cast<uint16_t *>(img.data() + L.tcol);
+            std::vector<uint64_t> next(L.nwin);
+            for (int w = 0; w < L.nwin; ++w) {
+                next[w] = (uint64_t)w * L.TW;
+                for (uint64_t p = std::min<uint64_t>((uint64_t)(w + 1) * L.TW, n); p < (uint64_t)(w + 1) * L.TW; ++p) {
+                    tlen[next[w]] = 0;
+                    tcol[next[w]++] = 0xFFFF;
+                }
+            }
+            for (uint64_t s = 0; s < (uint64_t)L.nb * L.CB; ++s) {
+                if (borig[s] < 0) continue;
+                const int w = borig[s] / L.TW;
+                tlen[next[w]] = blen[s];
+                tcol[next[w]++] = (uint16_t)(borig[s] - w * L.TW);
+            }
+        }
         uint32_t *wplanes = reinterpret_cast<uint32_t *>(img.data() + L.wplanes);
         for (int x = 0; x < A; ++x)
             for (int y = 0; y < A; ++y) {
@@ -604,7 +638,18 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     D.rg_off = reinterpret_cast<const uint32_t *>(base + L.rg_off);
     D.wplanes = reinterpret_cast<const uint32_t *>(base + L.wplanes);
     D.ccol = reinterpret_cast<const uint32_t *>(base + L.ccol);
-    e = narrow ? launch_column_layout(D, reinterpret_cast<uint32_t *>(base + L.ccol), st) : hipSuccess;
+    D.TW = L.TW;
+    D.nwin = L.nwin;
+    const bool windows = L.TW < L.CB;
+    D.tlen = windows ? base + L.tlen : D.blen;
+    D.tcol = windows ? reinterpret_cast<const uint16_t *>(base + L.tcol) : D.bcol;
+    D.tccol = windows ? reinterpret_cast<const uint32_t *>(base + L.tccol) : D.ccol;
+    if (narrow) {
+        e = launch_column_layout(D, D.blen, D.bcol, D.CB, (int64_t)L.nb * L.CB, reinterpret_cast<uint32_t *>(base + L.ccol), st);
+        if (e == hipSuccess && windows)
+            e = launch_column_layout(D, D.tlen, D.tcol, D.TW, (int64_t)L.nwin * L.TW,
+                                     reinterpret_cast<uint32_t *>(base + L.tccol), st);
+    }
     const hipError_t es = hipStreamSynchronize(st);   // the copy reads img: wait in any case
     if (e != hipSuccess || es != hipSuccess) return dev_fail(e != hipSuccess ? e : es, "copying the dictionary");
     v->h_gp_off = h_gp_off;

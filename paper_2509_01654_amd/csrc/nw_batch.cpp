@@ -312,18 +312,7 @@ int nw_batch_info(const nw_batch *B, uint64_t *items, uint32_t *launches)
     if (launches) {
         uint32_t n = 0;
         if (B->plan.width == 0) {   // as launch_triangle_tiled issues them
-            for (const nw_vocab *x : B->v) {
-                if (x->n < 2) continue;
-                if ((int64_t)x->n <= kClassLaunchMaxWords) {
-                    for (size_t c = 0; c < x->h_maxrp.size(); c += 8) {
-                        uint32_t rows = 0;
-                        for (size_t la = c; la < std::min(c + 8, x->h_maxrp.size()); ++la) rows += x->h_maxrp[la];
-                        n += rows > 0;
-                    }
-                } else {
-                    for (uint32_t c : x->h_maxrp) n += c > 0;
-                }
-            }
+            for (const nw_vocab *x : B->v) n += triangle_launches(x->dev, x->h_maxrp.data(), B->out_kind);
         } else {
             for (size_t c = 0; c + 1 < B->plan.class_off.size(); ++c) n += B->plan.class_off[c + 1] > B->plan.class_off[c];
         }

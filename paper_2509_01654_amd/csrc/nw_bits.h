@@ -42,6 +42,8 @@
 
 namespace nw {
 
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
 constexpr int kBitRows = 32;                     // row words of a group
 constexpr int kColDwords = kWordBytes / 4;       // symbol dwords of a column word
 
@@ -155,7 +157,8 @@ __host__ __device__ constexpr uint32_t bit_tab_bytes(int LA, int tab, int alphab
 // lane l at ccol[(group * kColDwords + q) * 64 + l]; the symbols start
 // (longest - own length) bytes in, the bytes before and after are symbol 0.
 struct ColWords {
-    const uint32_t *p;   // this lane's dword 0
+    const uint32_t *p;   // lane 0's dword 0 (wave-uniform)
+    uint32_t dw0;        // this lane's dword 0
     int ncols;           // longest word of the 64 (wave-uniform)
     int npad;            // ncols - shortest (wave-uniform)
     int lb;              // this lane's length
@@ -218,6 +221,7 @@ struct BitColumn {
     // Run the columns of the lane's word against the table at LDS address tab.
     __device__ __forceinline__ void run(const ColWords &W, uint32_t tab)
     {
+        const uint32_t lane = threadIdx.x & 63u;
 #pragma unroll
         for (int i = 0; i < LA; ++i)
 #pragma unroll
@@ -228,33 +232,29 @@ struct BitColumn {
             const int nc = W.ncols;
             if (nc == 0) return;
             const int first = nc - W.lb;   // the lane's first real column
-            uint32_t dw = W.p[0];
+            // one column a trip (a longer loop body costs instruction cache:
+            // a launch runs many lengths); the symbol after the last is one
+            // of the word's or 0, in either case a row of the table
+            const int lastq = (nc - 1) >> 2;
+            uint32_t dw = W.dw0, dn = W.p[(uint32_t)(64 * min(1, lastq)) + lane];
             u32x4 row[NW];
-            uint32_t r0 = tv + (dw & 0xFFu) * RB;
-            load_row<NW>(row, r0);
-            // trips of four columns (past the last column the bytes are symbol
-            // 0, a row of the table)
-            for (int c = 0; c < nc; c += 4) {
-                const uint32_t dn = W.p[64 * min((c >> 2) + 1, (nc - 1) >> 2)];
-                const uint32_t r1 = tv + ((dw >> 8) & 0xFFu) * RB;
-                if (c == 0)
-                    column<true>(row, r0, r1);
-                else
-                    column<false>(row, r0, r1);
+            uint32_t cur = tv + (dw & 0xFFu) * RB;
+            load_row<NW>(row, cur);
+            dw >>= 8;
+            uint32_t next = tv + (dw & 0xFFu) * RB;
+            column<true>(row, cur, next);
+            if (0 < W.npad) reset_unless(first <= 0);
+            for (int c = 1; c < nc; ++c) {
+                if ((c & 3) == 3) {
+                    dw = dn;
+                    dn = W.p[(uint32_t)(64 * min((c >> 2) + 2, lastq)) + lane];
+                } else {
+                    dw >>= 8;
+                }
+                cur = next;
+                next = tv + (dw & 0xFFu) * RB;
+                column<false>(row, cur, next);
                 if (c < W.npad) reset_unless(c >= first);
-                if (c + 1 >= nc) break;
-                const uint32_t r2 = tv + ((dw >> 16) & 0xFFu) * RB;
-                column<false>(row, r1, r2);
-                if (c + 1 < W.npad) reset_unless(c + 1 >= first);
-                if (c + 2 >= nc) break;
-                const uint32_t r3 = tv + (dw >> 24) * RB;
-                column<false>(row, r2, r3);
-                if (c + 2 < W.npad) reset_unless(c + 2 >= first);
-                if (c + 3 >= nc) break;
-                r0 = tv + (dn & 0xFFu) * RB;
-                column<false>(row, r3, r0);
-                if (c + 3 < W.npad) reset_unless(c + 3 >= first);
-                dw = dn;
             }
         }
     }
@@ -267,7 +267,7 @@ struct BitColumn {
         for (int i = 0; i < LA; ++i) {
             const uint32_t m = rowmask[i];
 #pragma unroll
-            for (int q = 0; q < S::kPlanes; ++q) v[i][q] = (v[i][q] & m) | ((pabs >> q & 1) ? ~m : 0u);
+            for (int q = 0; q < S::kPlanes; ++q) v[i][q] = lut3<kMux>(m, v[i][q], (uint32_t)-(pabs >> q & 1));
         }
     }
 
@@ -400,14 +400,14 @@ __device__ __forceinline__ BitGroup bit_group(uint8_t *base, int alphabet)
     return G;
 }
 
-// Build the groups first .. first+n-1 (global group numbers: slots 32 g ..
-// 32 g + 31, block origin I0) into lds, `stride` bytes apart.  All threads of
+// Build n groups into lds, `stride` bytes apart.  slot_of(g, b) is the slot
+// of row word b of group g (block origin I0), -1 for none.  All threads of
 // the workgroup call it; the caller's barrier after it completes the build.
-// It starts with a barrier-separated clear, so no thread may still read the
-// old groups when it is entered.
-template <int LA, class S, int NT>
-__device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint32_t first, int n, uint8_t *lds,
-                                             uint32_t stride)
+// It clears the tables first, so no thread may still read the old groups
+// when it is entered.
+template <int LA, class S, int NT, typename SlotOf>
+__device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, int n, uint8_t *lds, uint32_t stride,
+                                             SlotOf slot_of)
 {
     // kept from hoisting the addresses of the build over the caller's loop
     const int tid = (int)in_vgpr(threadIdx.x);
@@ -424,8 +424,8 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint
         for (int x = tid; x < n * LA * kBitRows; x += NT) {
             const int b = x & (kBitRows - 1), gi = x >> 5;
             const int i = gi % LA, g = gi / LA;
-            const int64_t slot = ((int64_t)first + g) * kBitRows + b;
-            if (i < (int)V.blen[slot]) {
+            const int64_t slot = slot_of(g, b);
+            if (slot >= 0 && i < (int)V.blen[slot]) {
                 const uint32_t c = V.bsym[slot * V.WB + i];
                 uint32_t *t = reinterpret_cast<uint32_t *>(lds + (uint32_t)g * stride);
                 atomicOr(&t[c * RD + (uint32_t)i], 1u << b);
@@ -445,9 +445,10 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint
             uint32_t m[32];
 #pragma unroll
             for (int b = 0; b < 32; ++b) {
-                const int64_t slot = ((int64_t)first + g) * kBitRows + b;
-                const uint32_t s = V.bsym[slot * V.WB + i];
-                m[b] = i < (int)V.blen[slot] ? V.wplanes[(s * 3u + (uint32_t)q) * 8u + (uint32_t)hf] : 0u;
+                const int64_t slot = slot_of(g, b);
+                m[b] = 0u;
+                if (slot >= 0 && i < (int)V.blen[slot])
+                    m[b] = V.wplanes[((uint32_t)V.bsym[slot * V.WB + i] * 3u + (uint32_t)q) * 8u + (uint32_t)hf];
             }
             transpose32(m);
             uint32_t *t = reinterpret_cast<uint32_t *>(lds + (uint32_t)g * stride);
@@ -458,8 +459,8 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint
     }
     for (int x = tid; x < n * kBitRows; x += NT) {
         const int g = x >> 5, b = x & (kBitRows - 1);
-        const int64_t slot = ((int64_t)first + g) * kBitRows + b;
-        const uint32_t col = V.bcol[slot];
+        const int64_t slot = slot_of(g, b);
+        const uint32_t col = slot >= 0 ? (uint32_t)V.bcol[slot] : 0xFFFFu;
         BitGroup G = bit_group<LA, S>(lds + (uint32_t)g * stride, A);
         G.cu[b] = col == 0xFFFFu ? -1 : (int32_t)(I0 + col);
     }
@@ -469,7 +470,8 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint
         const int half = lane >> 5, b = lane & 31;
         for (int x = tid >> 6; x < (n + 1) / 2; x += NT / 64) {
             const int g = 2 * x + half;
-            const int len = g < n ? (int)V.blen[((int64_t)first + g) * kBitRows + b] : 0;
+            const int64_t slot = g < n ? slot_of(g, b) : -1;
+            const int len = slot >= 0 ? (int)V.blen[slot] : 0;
             uint32_t m0 = 0, m1 = 0;
 #pragma unroll
             for (int i = 0; i < LA; ++i) {
@@ -486,14 +488,26 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, uint
     }
 }
 
-// The column words of 64 slots (column-slot group cg, global) for this lane.
-__device__ __forceinline__ ColWords col_words(const DevVocab &V, int64_t cg, int lane)
+// The column words of 64 slots (group cg of the column array ccol, lengths
+// clen) for this lane: the loads, and then the wave-uniform lengths.
+__device__ __forceinline__ ColWords col_words_load(const uint32_t *ccol, const uint8_t *clen, int64_t cg, int lane)
 {
     ColWords W;
-    W.p = V.ccol + cg * (kColDwords * 64) + lane;
-    W.lb = V.blen[cg * 64 + lane];
+    W.p = ccol + cg * (kColDwords * 64);
+    W.dw0 = W.p[(uint32_t)lane];
+    W.lb = (clen + cg * 64)[(uint32_t)lane];
+    W.ncols = W.npad = 0;
+    return W;
+}
+__device__ __forceinline__ void col_words_lengths(ColWords &W)
+{
     W.ncols = __builtin_amdgcn_readlane(W.lb, 63);
     W.npad = W.ncols - __builtin_amdgcn_readfirstlane(W.lb);
+}
+__device__ __forceinline__ ColWords col_words(const uint32_t *ccol, const uint8_t *clen, int64_t cg, int lane)
+{
+    ColWords W = col_words_load(ccol, clen, cg, lane);
+    col_words_lengths(W);
     return W;
 }
 
@@ -502,16 +516,19 @@ __device__ __forceinline__ ColWords col_words(const DevVocab &V, int64_t cg, int
 constexpr int kBitClasses = kMaxLen / 4;
 __host__ __device__ constexpr int bit_class_lo(int C) { return C == 0 ? 0 : 4 * C + 1; }
 __host__ __device__ constexpr int bit_class_hi(int C) { return 4 * C + 4; }
-template <int C, typename F>
-__device__ __forceinline__ void bit_class_dispatch(int LA, F &&f)
+// f(integral_constant<int, LA>) for the (wave-uniform) LA in [LO, HI].
+template <int LO, int HI, typename F>
+__device__ __forceinline__ void bit_length_dispatch(int LA, F &&f)
 {
-    if constexpr (C == 0) {
-        if (LA == 0) return f(std::integral_constant<int, 0>{});
+    if constexpr (LO == HI) {
+        f(std::integral_constant<int, LO>{});
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (LA <= MID)
+            bit_length_dispatch<LO, MID>(LA, f);
+        else
+            bit_length_dispatch<MID + 1, HI>(LA, f);
     }
-    if (LA == 4 * C + 1) return f(std::integral_constant<int, 4 * C + 1>{});
-    if (LA == 4 * C + 2) return f(std::integral_constant<int, 4 * C + 2>{});
-    if (LA == 4 * C + 3) return f(std::integral_constant<int, 4 * C + 3>{});
-    return f(std::integral_constant<int, 4 * C + 4>{});
 }
 
 }  // namespace nw

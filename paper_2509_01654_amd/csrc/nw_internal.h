@@ -85,6 +85,15 @@ struct DevVocab {
     const uint32_t *rg_off;     // [nb*(LMAX+1)+1]
     const uint32_t *ccol;       // [nb*CB/64][12][64]
     const uint32_t *wplanes;    // [256][3][8]
+    // Column windows of the bit-plane triangle: TW consecutive caller-order
+    // words (TW divides CB), sorted like a block.  Slot s (global: window *
+    // TW + local) holds word window * TW + tcol[s] (0xFFFF for padding slots,
+    // first), of length tlen[s]; tccol has their words like ccol.
+    int32_t TW;
+    int32_t nwin;
+    const uint8_t *tlen;        // [nwin*TW]
+    const uint16_t *tcol;       // [nwin*TW]
+    const uint32_t *tccol;      // [nwin*TW/64][12][64]
 };
 
 enum OutKind { OUT_I8 = 1, OUT_I16 = 2, OUT_EDGES = 3 };
@@ -106,8 +115,10 @@ struct EdgeSink {
     int32_t lo, hi, den;
 };
 
-// Write the ccol array of a loaded dictionary (from bsym and blen).
-hipError_t launch_column_layout(const DevVocab &V, uint32_t *ccol, hipStream_t stream);
+// Write a column array (ccol or tccol) of nslots slots in windows of `window`
+// caller-order words, from csym.
+hipError_t launch_column_layout(const DevVocab &V, const uint8_t *len, const uint16_t *col, int window, int64_t nslots,
+                                uint32_t *ccol, hipStream_t stream);
 
 // Launchers.  Each enqueues on `stream` and returns the hipError_t of the
 // launches.  Launchers with one launch per row length (or class) spread those
@@ -128,6 +139,11 @@ class StreamFork;
 hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
                                  int out_kind, void *d_out, hipStream_t stream, const EdgeSink *E = nullptr,
                                  StreamFork *shared = nullptr);
+// The same for dictionaries the bit-plane kernels hold (triangle_bits_applies),
+// int8 / int16 scores only; h_maxrp tells the lengths present.
+bool triangle_bits_applies(const DevVocab &V, int out_kind);
+// Launches launch_triangle_tiled issues for a whole triangle.
+uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind);
 hipError_t launch_triangle_naive(const DevVocab &V, uint64_t idx_begin, uint64_t idx_end, int out_kind,
                                  void *d_out, hipStream_t stream, const EdgeSink *E = nullptr);
 // Threshold edges of pair indices [idx_begin, idx_end) into E, scored and

@@ -7,6 +7,8 @@ half-filled groups, alphabets on both sides of a 32-symbol mask, and scorings on
 both sides of every rule that picks 2 planes, 3 planes or the packed kernels.
 Scores are integers: no tolerance.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -105,3 +107,62 @@ def test_topk_bits_group_edges(n):
         assert np.array_equal(sc.cpu().numpy()[r0:r1].astype(np.int32), ws)
         assert np.array_equal(ix.cpu().numpy()[r0:r1], wi)
     assert int(h.sum()) == n * (n - 1) // 2
+
+
+def _ranges(n, pairs, rng):
+    """Whole triangle, single pairs, parts of one row, row ends, ranges over a few rows and over many."""
+    start = lambda u: u * (2 * n - u - 1) // 2
+    out = [(0, pairs), (0, 1), (pairs - 1, pairs), (start(3) + 2, start(3) + 9), (start(5), start(6)),
+           (start(n // 2) + 1, start(n // 2 + 40) + 3)]
+    for _ in range(4):
+        a, b = sorted(rng.integers(0, pairs + 1, size=2).tolist())
+        out.append((a, b))
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["int8", "int16"])
+@pytest.mark.parametrize("name", list(SCORINGS))
+@pytest.mark.parametrize("n,lmax", [(333, 48), (530, 11), (140, 36)])
+def test_triangle_bits(name, n, lmax, dtype):
+    """Every range and output alignment (bytes before the first element) against the oracle."""
+    nw, torch = _nw()
+    v = _words(n, SCORINGS[name][0], lmax, seed=6)
+    dv, sim, gap = _load(name, v)
+    dt, es = (torch.int8, 1) if dtype == "int8" else (torch.int16, 2)
+    if dtype == "int8" and not (dv.bounds[0] >= -128 and dv.bounds[1] <= 127):
+        with pytest.raises(nw.NwError):
+            dv.all_pairs_scores(dtype=dt)
+        return
+    want = oracle.triangle(v.symbols, v.offsets, sim, gap)
+    pairs = want.size
+    for q, (a, b) in enumerate(_ranges(n, pairs, np.random.default_rng(n))):
+        shift = q % 4
+        buf = torch.full(((b - a) * es + 16,), 0x55, dtype=torch.uint8, device="cuda:0")
+        rc = nw._lib.nw_all_pairs_scores(dv._h, a, b, es, ctypes.c_void_p(buf.data_ptr() + shift),
+                                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == nw.NW_OK
+        torch.cuda.synchronize()
+        host = buf.cpu().numpy()
+        got = host[shift:shift + (b - a) * es].copy().view(np.int8 if es == 1 else np.int16)
+        assert np.array_equal(got.astype(np.int64), want[a:b]), (a, b, shift)
+        assert (host[:shift] == 0x55).all() and (host[shift + (b - a) * es:] == 0x55).all(), (a, b, shift)
+
+
+@pytest.mark.parametrize("n,lmax", [(17000, 14), (40000, 20), (33000, 30)])
+def test_triangle_bits_windows(n, lmax):
+    """Blocks of 1024, 2048 words and windows of 1024: a few rows, whole and cut, against the oracle."""
+    _, torch = _nw()
+    v = zipf_vocab(n, seed=n, mean_len=7.0, min_len=0, max_len=lmax)
+    dv, sim, gap = _load("plain", v)
+    start = lambda u: u * (2 * n - u - 1) // 2
+    out = dv.all_pairs_scores(dtype=torch.int8)
+    torch.cuda.synchronize()
+    for u in (0, 1023, 1024, 2047, 2048, n // 2, n - 1025, n - 2):
+        want = oracle.triangle(v.symbols, v.offsets, sim, gap, start(u), start(u + 1))
+        assert np.array_equal(out[start(u):start(u + 1)].cpu().numpy().astype(np.int32), want), u
+    a, b = start(1000) + 5, start(1100) + 7
+    part = dv.all_pairs_scores(a, b, dtype=torch.int8)
+    assert torch.equal(part, out[a:b])
+    a, b = start(n // 3) + 100, start(n // 3 + 3000) + 7
+    part = dv.all_pairs_scores(a, b, dtype=torch.int16)
+    assert torch.equal(part, out[a:b].to(torch.int16))
