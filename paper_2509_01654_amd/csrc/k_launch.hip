@@ -12,6 +12,7 @@
 #include "k_batch.h"
 #include "k_diag.h"
 #include "k_edges.h"
+#include "k_edges_bits.h"
 #include "k_probe.h"
 #include "k_query.h"
 #include "k_topk.h"
@@ -191,15 +192,15 @@ bool triangle_bits_applies(const DevVocab &V, int out_kind)
     return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16) <= kMaxLdsBytes;
 }
 
-// The launches of a bit-plane triangle over the lengths present in h_maxrp:
-// ranges of row lengths (tri_bits_span), the longest rows first.
+// The launches of a bit-plane triangle or edge call over the lengths present in h_maxrp:
+// ranges of row lengths (bits_span), the longest rows first.
 struct LengthRange {
     int lo, hi, range;
 };
-static std::vector<LengthRange> triangle_bits_launches(const DevVocab &V, const uint32_t *h_maxrp)
+static std::vector<LengthRange> bits_launches(const DevVocab &V, const uint32_t *h_maxrp)
 {
     std::vector<LengthRange> out;
-    const int span = V.bits == 2 ? tri_bits_span<Bits2>() : tri_bits_span<Bits3>();
+    const int span = V.bits == 2 ? bits_span<Bits2>() : bits_span<Bits3>();
     for (int r = (V.lmax - 1) / span; r >= 0; --r) {
         int lo = r == 0 ? 0 : r * span + 1, hi = std::min((r + 1) * span, (int)V.lmax);
         while (lo <= hi && h_maxrp[lo] == 0) ++lo;
@@ -233,7 +234,7 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
         return most;
     };
     constexpr uint64_t kWorkgroups = 8192;
-    const std::vector<LengthRange> launches = triangle_bits_launches(V, h_maxrp);
+    const std::vector<LengthRange> launches = bits_launches(V, h_maxrp);
     uint64_t chunks = 0;
     for (const LengthRange &L : launches) chunks += (uint64_t)parts(L) * (uint64_t)(L.hi - L.lo + 1);
     int nw = (int)std::max<uint64_t>(1, std::min<uint64_t>(8, chunks * nr * V.nwin / 2 / kWorkgroups));
@@ -255,7 +256,7 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
 uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind)
 {
     if (V.n < 2) return 0;
-    if (triangle_bits_applies(V, out_kind)) return (uint32_t)triangle_bits_launches(V, h_maxrp).size();
+    if (triangle_bits_applies(V, out_kind)) return (uint32_t)bits_launches(V, h_maxrp).size();
     const int per = V.n <= kClassLaunchMaxWords ? 8 : 1;
     uint32_t launches = 0;
     for (int lo = 0; lo <= V.lmax; lo += per) {
@@ -351,6 +352,23 @@ hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uin
     return shared ? hipSuccess : own.end();
 }
 
+// Parts the 64-word column steps of a tile are dealt to: a launch of few tiles
+// (each one workgroup per row length) halves them until it has 384, or four
+// steps, one per wavefront, are left.  20k words (210 tiles): main pass
+// 0.53 -> 0.35 ms; 30k words with a matrix (465 tiles, larger tables to
+// build): 3.7 ms whole, 4.0 ms in three parts.
+static int col_splits(uint64_t tiles, int CB)
+{
+    int s = 1;
+    while (tiles * s < 384 && 2 * s <= CB / 256) s *= 2;
+    return s;
+}
+
+static bool edges_bits_applies(const DevVocab &V)
+{
+    return V.bits != 0 && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V) <= kMaxLdsBytes;
+}
+
 hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
                               const EdgeSink &E, hipStream_t stream)
 {
@@ -360,6 +378,22 @@ hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64
     StreamFork fork(stream);
     hipError_t ef = fork.begin();
     if (ef != hipSuccess) return ef;
+    if (edges_bits_applies(V)) {
+        for (const LengthRange &L : bits_launches(V, h_maxrp)) {
+            DevVocab Vc = V;
+            EdgeSink Ec = E;
+            uint64_t ib = idx_begin, ie = idx_end;
+            uint32_t rb0 = G.rb0, rbn = G.rbn;
+            int splits = col_splits(G.blocks, V.CB), hi = L.hi;
+            uint32_t lds = edges_bits_lds_bytes(hi, bit_tab(V), bit_wmax(V), V);
+            void *args[] = {&Vc, &Ec, &ib, &ie, &rb0, &rbn, &splits, &hi, &lds};
+            hipError_t e = launch_dyn(tab.edges_bits[V.bits - 2][L.range],
+                                      dim3((uint32_t)((uint64_t)G.blocks * splits), (uint32_t)(L.hi - L.lo + 1)), lds,
+                                      fork, args);
+            if (e != hipSuccess) return e;
+        }
+        return fork.end();
+    }
     for (int LA = 0; LA <= V.lmax; ++LA) {
         if (h_maxrp[LA] == 0) continue;
         uint32_t chunks = tile_chunks(G.blocks, h_maxrp[LA]);
@@ -582,18 +616,6 @@ hipError_t launch_column_layout(const DevVocab &V, const uint8_t *len, const uin
     hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((ndw + 255) / 256)), dim3(256), 0, stream, V.csym, len, col,
                        window, V.WB, ndw, ccol);
     return hipGetLastError();
-}
-
-// Parts the 64-word column steps of a tile are dealt to: a launch of few tiles
-// (each one workgroup per row length) halves them until it has 384, or four
-// steps, one per wavefront, are left.  20k words (210 tiles): main pass
-// 0.53 -> 0.35 ms; 30k words with a matrix (465 tiles, larger tables to
-// build): 3.7 ms whole, 4.0 ms in three parts.
-static int col_splits(uint64_t tiles, int CB)
-{
-    int s = 1;
-    while (tiles * s < 384 && 2 * s <= CB / 256) s *= 2;
-    return s;
 }
 
 // The main pass takes the bit-plane kernels where the scoring fits them and

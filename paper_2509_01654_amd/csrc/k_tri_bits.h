@@ -372,29 +372,11 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
     }
 }
 
-// Row lengths of one launch, all in one kernel: a launch ends with the
-// workgroups of its last lengths alone on the chip, so few and full launches
-// win (50k words of up to 20 symbols: one launch of 0 .. 24 against five of
-// four lengths each), as far as the registers of the longest rows leave the
-// short ones the waves that LDS admits.
-template <class S>
-constexpr int tri_bits_span() { return S::kPlanes == 2 ? 24 : 12; }
-template <class S>
-constexpr int tri_bits_ranges() { return kMaxLen / tri_bits_span<S>(); }
-
-// Waves per SIMD asked of the compiler: what its registers hold without
-// spilling inside the column loop.
-template <int HI, class S>
-constexpr int tri_bits_min_waves()
-{
-    return S::kPlanes == 2 ? (HI <= 24 ? 4 : 1) : (HI <= 12 ? 4 : HI <= 24 ? 3 : 1);
-}
-
 // Longest row lengths LO .. HI, one per blockIdx.y, the longest first;
 // blockIdx.x = (row block - rb0) * nset + set, set s being the windows s * nw
 // .. s * nw + nw - 1; blockIdx.z = the part of the groups.
 template <int LO, int HI, class S, int ES, bool W16>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(tri_bits_min_waves<HI, S>())))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bits_min_waves<HI, S>())))
 void k_tri_bits(DevVocab V, uint64_t idx_begin, uint64_t idx_end, void *out, uint32_t rb0, uint32_t nset, int nw,
                 int hi, uint32_t lds_bytes)
 {

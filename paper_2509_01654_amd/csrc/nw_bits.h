@@ -531,4 +531,23 @@ __device__ __forceinline__ void bit_length_dispatch(int LA, F &&f)
     }
 }
 
+// Row lengths of one launch of the triangle and edge kernels, all in one
+// kernel: a launch ends with the
+// workgroups of its last lengths alone on the chip, so few and full launches
+// win (50k words of up to 20 symbols: one launch of 0 .. 24 against five of
+// four lengths each), as far as the registers of the longest rows leave the
+// short ones the waves that LDS admits.
+template <class S>
+constexpr int bits_span() { return S::kPlanes == 2 ? 24 : 12; }
+template <class S>
+constexpr int bits_ranges() { return kMaxLen / bits_span<S>(); }
+
+// Waves per SIMD asked of the compiler: what its registers hold without
+// spilling inside the column loop.
+template <int HI, class S>
+constexpr int bits_min_waves()
+{
+    return S::kPlanes == 2 ? (HI <= 24 ? 4 : 1) : (HI <= 12 ? 4 : HI <= 24 ? 3 : 1);
+}
+
 }  // namespace nw

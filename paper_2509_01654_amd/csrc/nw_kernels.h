@@ -16,8 +16,8 @@ constexpr int kNumClass8 = 7;
 // Classes of four lengths of the bit-plane kernels, by translation unit.
 #define NW_BITS_SPLITS X(0, 1) X(2, 2) X(3, 3) X(4, 4) X(5, 5) X(6, 6) X(7, 7) X(8, 8) X(9, 9) X(10, 10) X(11, 11)
 
-// Bit-plane triangle kernels: translation units (variant, range of lengths).
-#define NW_TRI_BITS X(0, 0) X(0, 1) X(1, 0) X(1, 1) X(2, 0) X(2, 1) X(2, 2) X(2, 3) X(3, 0) X(3, 1) X(3, 2) X(3, 3) X(4, 0) X(4, 1) X(4, 2) X(4, 3)
+// Bit-plane triangle and edge kernels: translation units (variant, range of lengths).
+#define NW_TRI_BITS X(0, 0) X(0, 1) X(1, 0) X(1, 1) X(2, 0) X(2, 1) X(2, 2) X(2, 3) X(3, 0) X(3, 1) X(3, 2) X(3, 3) X(4, 0) X(4, 1) X(4, 2) X(4, 3) X(5, 0) X(5, 1) X(6, 0) X(6, 1) X(6, 2) X(6, 3)
 
 struct KernelTables {
     const void *tri[kMaxLen + 1];
@@ -30,6 +30,7 @@ struct KernelTables {
     const void *topk_bits[2][2][kMaxLen / 4];   // bit planes, classes of 4 lengths: [Bits2, Bits3][without, with histogram]
     // triangle: Bits2 int8, Bits2 int16, Bits3 int8, Bits3 int16, Bits3 int16 with 16-bit staging
     const void *tri_bits[5][4];                 // [variant][range of lengths]
+    const void *edges_bits[2][4];               // threshold edges: Bits2, Bits3
     const void *edges[kMaxLen + 1];      // threshold edge emitter
     const void *persist1[kMaxLen + 1];   // persistent batched kernel, one per row length
     const void *persist8[kNumClass8];    // persistent batched kernel, one per class of 8 lengths

@@ -166,3 +166,26 @@ def test_triangle_bits_windows(n, lmax):
     a, b = start(n // 3) + 100, start(n // 3 + 3000) + 7
     part = dv.all_pairs_scores(a, b, dtype=torch.int16)
     assert torch.equal(part, out[a:b].to(torch.int16))
+
+
+@pytest.mark.parametrize("name", list(SCORINGS))
+@pytest.mark.parametrize("n,lmax", [(333, 48), (530, 11)])
+def test_edges_bits(name, n, lmax):
+    """Raw and normalised slices, counting alone, a capacity below the count, ranges and a dense slice."""
+    _, torch = _nw()
+    v = _words(n, SCORINGS[name][0], lmax, seed=8)
+    dv, sim, gap = _load(name, v)
+    pairs = n * (n - 1) // 2
+    lo, hi = dv.bounds
+    slices = [(hi // 2, hi, False, 1), (lo, hi, False, 1), (hi + 1, hi + 5, False, 1), (60, 100, True, 1), (200, 400, True, 3),
+              (-350, -10, True, 2), (-1000000, 1000000, True, 1)]
+    for q, (a, b, norm, den) in enumerate(slices):
+        for i0, i1 in ([(0, pairs)] if q else [(0, pairs), (pairs // 3 + 1, pairs // 2 + 7), (5, 6)]):
+            ei, ej, es = oracle.edges(v.symbols, v.offsets, sim, gap, a, b, normalised=norm, den=den, idx_begin=i0, idx_end=i1)[:3]
+            i, j, s, count = dv.all_pairs_edges(a, b, normalised=norm, den=den, idx_begin=i0, idx_end=i1)
+            assert count == len(ei)
+            got = sorted(zip(i.tolist(), j.tolist(), s.tolist()))
+            assert got == sorted(zip(map(int, ei), map(int, ej), map(int, es)))
+            if count > 10:
+                i, j, s, count2 = dv.all_pairs_edges(a, b, normalised=norm, den=den, idx_begin=i0, idx_end=i1, cap=count - 7)
+                assert count2 == count and set(zip(i.tolist(), j.tolist(), s.tolist())) <= set(got)
