@@ -197,6 +197,10 @@ hipError_t launch_scatter_lists(const int16_t *qs, const int32_t *qi, const int3
 struct TopkArgs;
 hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream);
 
+// dst[0 .. bytes) (device) = src (host), carried as kernel arguments: nothing on
+// the host has to outlive the call.  For images of a few KiB.
+hipError_t launch_upload(void *dst, const void *src, uint64_t bytes, hipStream_t stream);
+
 // Zero n counters (a kernel, so graph capture records no memset node).
 hipError_t launch_reset_counters(uint32_t *counters, int n, hipStream_t stream);
 

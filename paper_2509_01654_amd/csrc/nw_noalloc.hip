@@ -28,20 +28,6 @@ namespace {
 constexpr uint32_t kNoAllocMaxQueries = 256;
 // Host image of at most kNoAllocMaxQueries rows (words, pairs, offsets, rows).
 constexpr uint64_t kImageBytes = 20u << 10;
-// Bytes carried by one upload launch (kernel arguments are at most 4 KiB).
-constexpr uint32_t kChunkBytes = 3072;
-
-struct UploadChunk {
-    uint32_t off, n;
-    uint8_t bytes[kChunkBytes];
-};
-
-// dst[c.off .. c.off + c.n) = c.bytes[0 .. c.n)
-__global__ __launch_bounds__(256) void k_upload(uint8_t *dst, UploadChunk c)
-{
-    for (uint32_t i = threadIdx.x; i < c.n; i += blockDim.x) dst[c.off + i] = c.bytes[i];
-}
-
 // The device address of `scratch` on device `dev`, looked up once per device
 // (with that device current) and kept.
 hipError_t scratch_of(int dev, uint8_t **out)
@@ -131,14 +117,7 @@ extern "C" int nw_query_noalloc(const nw_vocab *v, const uint8_t *h_q_symbols, c
     if (e != hipSuccess) return dev_fail(e, "looking up the query scratch");
     // the image goes up as kernel arguments: nothing on the host has to
     // outlive the call
-    for (uint32_t o = 0; o < W.partial; o += kChunkBytes) {
-        UploadChunk c;
-        c.off = o;
-        c.n = (uint32_t)std::min<uint64_t>(kChunkBytes, W.partial - o);
-        std::memcpy(c.bytes, img + o, c.n);
-        hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, st, ws, c);
-        if ((e = hipGetLastError()) != hipSuccess) return dev_fail(e, "uploading queries");
-    }
+    if ((e = launch_upload(ws, img, W.partial, st)) != hipSuccess) return dev_fail(e, "uploading queries");
     RowSet R;
     R.sym = ws + W.sym;
     R.pairs = reinterpret_cast<const int32_t *>(ws + W.pairs);
