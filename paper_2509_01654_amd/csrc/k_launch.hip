@@ -102,13 +102,14 @@ const KernelTables &kernel_tables()
 }
 
 // A launch through a fork (a stream, or a node of the graph being captured).
-static hipError_t launch_dyn(const void *fn, dim3 grid, size_t lds, StreamFork &fork, void **args)
+static hipError_t launch_dyn(const void *fn, dim3 grid, size_t lds, StreamFork &fork, void **args,
+                             int threads = kThreads)
 {
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    return fork.launch(fn, grid, dim3(kThreads), lds, args);
+    return fork.launch(fn, grid, dim3(threads), lds, args);
 }
 
 // Row of pair index idx in the row-major triangle of n words: the largest u
@@ -247,7 +248,8 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
         int hi = L.hi;
         void *args[] = {&Vc, &ib, &ie, &po, &rb0, &nset, &nw, &hi, &lds};
         hipError_t e = launch_dyn(tab.tri_bits[scheme][L.range],
-                                  dim3(nr * nset, (uint32_t)(L.hi - L.lo + 1), parts(L)), lds, fork, args);
+                                  dim3(nr * nset, (uint32_t)(L.hi - L.lo + 1), parts(L)), lds, fork, args,
+                                  tab.tri_bits_threads[scheme][L.range]);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -123,7 +123,7 @@ __device__ __forceinline__ void store_eight(const TriRow &R, int f, const uint32
     }
 }
 
-template <int LA, class S, int ES, bool W16>
+template <int LA, class S, int ES, bool W16, int NT>
 __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uint32_t w0, int nw, uint32_t part, uint64_t idx_begin,
                                               uint64_t idx_end, void *out, uint32_t lds_bytes, uint8_t *lds)
 {
@@ -169,7 +169,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
     }
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    constexpr int NWAVE = kThreads / 64;
+    constexpr int NWAVE = NT / 64;
     const uint32_t lds0 = lds_addr_of(lds);
     const uint32_t SS = tri_stage_stride(TW);
     constexpr uint32_t SJ = W16 ? 16u : 8u;
@@ -193,9 +193,12 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
             const uint32_t col = V.bcol[I0 + s];
             return col != 0xFFFFu && I0 + col >= u0 && I0 + col < u1;
         };
-        const int per = V.CB / NWAVE;   // a multiple of 64
+        // the wavefronts' shares: a multiple of 64 slots (CB / 64 is at least
+        // 4 and, from 8 on, a multiple of NWAVE)
+        const int share = V.CB / min(NWAVE, V.CB / 64);
+        const int s0 = min(wave * share, V.CB), s1 = min(s0 + share, V.CB);
         uint32_t c = 0;
-        for (int s = wave * per; s < (wave + 1) * per; s += 64) c += (uint32_t)__popcll(__ballot(keep(s + lane)));
+        for (int s = s0; s < s1; s += 64) c += (uint32_t)__popcll(__ballot(keep(s + lane)));
         if (lane == 0) counts[wave] = c;
         if (tid < 2) counts[NWAVE + tid] = 0;
         __syncthreads();
@@ -204,7 +207,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
             if (q < wave) at += counts[q];
             nlist += counts[q];
         }
-        for (int s = wave * per; s < (wave + 1) * per; s += 64) {
+        for (int s = s0; s < s1; s += 64) {
             const bool k = keep(s + lane);
             const uint64_t m = __ballot(k);
             if (k)
@@ -215,7 +218,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
         __syncthreads();
         // groups of the list with a shorter, and with at most this, longest length
         const uint32_t ng = (nlist + kBitRows - 1) / kBitRows;
-        for (uint32_t g = tid; g < ng; g += kThreads) {
+        for (uint32_t g = tid; g < ng; g += NT) {
             const int len = V.blen[I0 + rows[min(g * kBitRows + kBitRows, nlist) - 1]];
             if (len < LA) atomicAdd(&counts[NWAVE], 1u);
             if (len <= LA) atomicAdd(&counts[NWAVE + 1], 1u);
@@ -239,12 +242,12 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
             if (!listed) return (int64_t)q;
             return q < nlist ? I0 + rows[q] : -1;
         };
-        build_groups<LA, S, kThreads>(V, I0, ng, groups, gstride, slot_of);
+        build_groups<LA, S, NT>(V, I0, ng, groups, gstride, slot_of);
         __syncthreads();
         for (int wi = 0; wi < nw; ++wi) {
         const uint32_t w = w0 + (uint32_t)wi;
         const int64_t J0 = (int64_t)w * TW, J1 = min(J0 + TW, n);
-        for (int x = tid; x < ng * kBitRows; x += kThreads) {
+        for (int x = tid; x < ng * kBitRows; x += NT) {
             const int64_t u = bit_group<LA, S>(groups + (uint32_t)(x >> 5) * gstride, A).cu[x & 31];
             TriRow R{0, 0, 0};
             if (u >= 0) {
@@ -258,7 +261,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
         __syncthreads();
         // this wavefront's steps, taken from either end in turn; the next
         // step's words are loaded while one runs
-        const int nq = (steps - 1 - wave) / NWAVE + 1;
+        const int nq = wave < steps ? (steps - 1 - wave) / NWAVE + 1 : 0;
         auto step_of = [&](int q) { return q * NWAVE + ((q & 1) && (q + 1) * NWAVE <= steps ? NWAVE - 1 - wave : wave); };
         auto load = [&](int q, ColWords &W, uint32_t &col) {
             const int st = step_of(q);
@@ -372,11 +375,18 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
     }
 }
 
+// Threads of a workgroup: eight wavefronts where the 64 KB of 16-bit staging
+// and the tables leave one workgroup per CU; four elsewhere (with eight for
+// every Bits3 row past 12 symbols, 20,000 words under a matrix took 1.15 ms
+// against 0.88: the registers then fit one workgroup instead of three).
+template <int HI, bool W16>
+constexpr int tri_bits_threads() { return W16 && HI > 12 ? 512 : 256; }
+
 // Longest row lengths LO .. HI, one per blockIdx.y, the longest first;
 // blockIdx.x = (row block - rb0) * nset + set, set s being the windows s * nw
 // .. s * nw + nw - 1; blockIdx.z = the part of the groups.
 template <int LO, int HI, class S, int ES, bool W16>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(bits_min_waves<HI, S>())))
+__global__ __launch_bounds__((tri_bits_threads<HI, W16>())) __attribute__((amdgpu_waves_per_eu(bits_min_waves<HI, S>())))
 void k_tri_bits(DevVocab V, uint64_t idx_begin, uint64_t idx_end, void *out, uint32_t rb0, uint32_t nset, int nw,
                 int hi, uint32_t lds_bytes)
 {
@@ -385,7 +395,7 @@ void k_tri_bits(DevVocab V, uint64_t idx_begin, uint64_t idx_end, void *out, uin
     const int LA = hi - (int)blockIdx.y;
     if (LA < LO || LA > HI) return;
     bit_length_dispatch<LO, HI>(LA, [&](auto la) {
-        tri_bits_tile<decltype(la)::value, S, ES, W16>(V, r, w0, nw, blockIdx.z, idx_begin, idx_end, out, lds_bytes, lds);
+        tri_bits_tile<decltype(la)::value, S, ES, W16, tri_bits_threads<HI, W16>()>(V, r, w0, nw, blockIdx.z, idx_begin, idx_end, out, lds_bytes, lds);
     });
 }
 

@@ -21,6 +21,7 @@ void NW_CAT(nw_fill_tri_bits_, NW_VARIANT, _, NW_RANGE)(KernelTables &t)
 {
 #if NW_VARIANT < 5
     t.tri_bits[NW_VARIANT][NW_RANGE] = reinterpret_cast<const void *>(&k_tri_bits<kLo, kHi, Scheme, kEs, NW_VARIANT == 4>);
+    t.tri_bits_threads[NW_VARIANT][NW_RANGE] = tri_bits_threads<kHi, NW_VARIANT == 4>();
 #else
     t.edges_bits[NW_VARIANT - 5][NW_RANGE] = reinterpret_cast<const void *>(&k_edges_bits<kLo, kHi, Scheme>);
 #endif

@@ -30,6 +30,7 @@ struct KernelTables {
     const void *topk_bits[2][2][kMaxLen / 4];   // bit planes, classes of 4 lengths: [Bits2, Bits3][without, with histogram]
     // triangle: Bits2 int8, Bits2 int16, Bits3 int8, Bits3 int16, Bits3 int16 with 16-bit staging
     const void *tri_bits[5][4];                 // [variant][range of lengths]
+    int tri_bits_threads[5][4];                 // and their threads per workgroup
     const void *edges_bits[2][4];               // threshold edges: Bits2, Bits3
     const void *edges[kMaxLen + 1];      // threshold edge emitter
     const void *persist1[kMaxLen + 1];   // persistent batched kernel, one per row length
