@@ -40,6 +40,7 @@ def _units():
     for variant, rng in _ranges("NW_TRI_BITS"):
         units.append((f"k_tri_bits_inst_{variant}_{rng}", os.path.join(CSRC, "k_tri_bits_inst.hip"),
                       [f"-DNW_VARIANT={variant}", f"-DNW_RANGE={rng}"]))
+    units.append(("k_probe_bits_inst", os.path.join(CSRC, "k_probe_bits_inst.hip"), []))
     units += [
         ("nw_api", os.path.join(CSRC, "nw_api.cpp"), []),
         ("nw_server", os.path.join(CSRC, "nw_server.cpp"), []),

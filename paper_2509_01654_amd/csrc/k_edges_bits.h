@@ -37,8 +37,7 @@ __host__ __device__ inline int edges_bits_groups(int LA, int tab, int wmax, int 
 __host__ __device__ inline uint32_t edges_bits_lds_bytes(int LA, int tab, int wmax, const DevVocab &V)
 {
     const uint32_t per = edges_bits_group_bytes(LA, tab, wmax, V.alphabet, V.lmax), fixed = edges_bits_fixed_bytes();
-    const uint32_t all = fixed + kBitMaxGroups * per;
-    return all <= kEdgeBitsLds ? all : fixed + per > kEdgeBitsLds ? fixed + per : kEdgeBitsLds;
+    return bit_lds_bytes(fixed, per, kEdgeBitsLds, (uint32_t)kBitMaxGroups);
 }
 
 // The scores of the slice for a pair whose longer word has m (>= 1) symbols:

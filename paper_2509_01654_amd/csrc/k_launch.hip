@@ -631,7 +631,7 @@ static bool topk_bits_applies(const DevVocab &V, const TopkArgs &T)
            topk_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, T.nbins, T.hist != nullptr) <= kMaxLdsBytes;
 }
 
-hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream)
+hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_bitlens, const TopkArgs &T, hipStream_t stream)
 {
     if (V.n < 2) return hipSuccess;
     const uint32_t nblk_pairs = (uint32_t)((uint64_t)V.nb * (V.nb + 1) / 2);
@@ -642,19 +642,21 @@ hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const To
     const bool bits = topk_bits_applies(V, T);
     if (bits) {
         const int h = T.hist != nullptr;
+        const uint64_t tiles = (uint64_t)nblk_pairs * (T.phase_hi - T.phase_lo + 1) / T.phase_mod;
+        const bool rect = T.phase_lo == T.phase_hi;
+        const uint32_t grid = rect ? (uint32_t)V.nb * ((uint32_t)(V.nb - T.phase_lo + T.phase_mod - 1) / (uint32_t)T.phase_mod)
+                                   : nblk_pairs;
+        if (rect && T.phase_lo >= V.nb) return fork.end();
         for (int c = 0; c < kBitClasses && bit_class_lo(c) <= V.lmax; ++c) {
-            const int lo = bit_class_lo(c), hi = std::min(bit_class_hi(c), (int)V.lmax);
-            uint32_t any = 0;
-            for (int LA = lo; LA <= hi; ++LA) any += h_maxrg[LA];
-            if (any == 0) continue;
+            if (h_bitlens[c] == 0) continue;
             DevVocab Vc = V;
             TopkArgs Tc = T;
-            Tc.bit_lds = topk_bits_lds_bytes(hi, bit_tab(V), bit_wmax(V), V, T.nbins, h);
-            Tc.col_splits = col_splits((uint64_t)nblk_pairs * (T.phase_hi - T.phase_lo + 1) / T.phase_mod, V.CB);
+            Tc.bit_lds = topk_bits_lds_bytes(std::min(bit_class_hi(c), (int)V.lmax), bit_tab(V), bit_wmax(V), V, T.nbins, h);
+            Tc.col_splits = col_splits(tiles, V.CB);
+            Tc.phase_rect = rect;
             void *args[] = {&Vc, &Tc};
-            hipError_t e = launch_dyn(tab.topk_bits[V.bits - 2][h][c],
-                                      dim3(nblk_pairs * (uint32_t)Tc.col_splits, (uint32_t)(hi - lo + 1)), Tc.bit_lds,
-                                      fork, args);
+            hipError_t e = launch_dyn(tab.topk_bits[V.bits - 2][h][c], dim3(grid * (uint32_t)Tc.col_splits, h_bitlens[c]),
+                                      Tc.bit_lds, fork, args);
             if (e != hipSuccess) return e;
         }
         return fork.end();

@@ -33,6 +33,9 @@ struct TopkArgs {
     int wt_in_lds;              // score-code kernel: 1 stages the similarity table in LDS
     // block pairs of this launch: (b - r) mod phase_mod in [phase_lo, phase_hi]
     int phase_mod, phase_lo, phase_hi;
+    // bit-plane kernels: 1 when the launch enumerates only block pairs with
+    // (b - r) mod phase_mod == phase_lo (tile = step * nb + r)
+    int phase_rect;
 };
 
 // The LDS histogram is kept in kHistCopies copies (copy = lane mod

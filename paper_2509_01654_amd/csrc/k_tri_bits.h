@@ -63,8 +63,7 @@ __host__ __device__ inline int tri_bits_groups(int LA, int tab, int alphabet, in
 __host__ __device__ inline uint32_t tri_bits_lds_bytes(int LA, int tab, const DevVocab &V, bool w16)
 {
     const uint32_t fixed = tri_bits_fixed_bytes(V.TW, V.CB, w16), per = tri_bits_group_bytes(LA, tab, V.alphabet);
-    const uint32_t all = fixed + kTriBitGroups * per;
-    return all <= kTriBitsLds ? all : fixed + per > kTriBitsLds ? fixed + per : kTriBitsLds;
+    return bit_lds_bytes(fixed, per, kTriBitsLds, (uint32_t)kTriBitGroups);
 }
 // More than 256 score values: 16-bit staging.
 __host__ __device__ inline bool tri_bits_wide(const DevVocab &V) { return V.hi - V.lo > 255; }

@@ -555,18 +555,20 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         }
     }
     // groups of 32 slots by their longest word (the last: slots are length-sorted)
-    std::vector<uint32_t> h_maxrg(LM + 1, 0);
+    std::vector<uint32_t> h_bitlens(kMaxLen / 4, 0);
     if (narrow) {
         uint32_t *rg_off = reinterpret_cast<uint32_t *>(img.data() + L.rg_off);
         const uint32_t per = (uint32_t)L.CB / 32;
         for (int blk = 0; blk < L.nb; ++blk) {
             uint32_t g = (uint32_t)blk * per;
+            uint32_t lens[kMaxLen / 4] = {};
             for (int l = 0; l <= LM; ++l) {
                 const uint32_t from = g;
                 rg_off[(size_t)blk * (LM + 1) + l] = from;
                 while (g < (uint32_t)(blk + 1) * per && blen[(size_t)g * 32 + 31] == l) ++g;
-                h_maxrg[l] = std::max(h_maxrg[l], g - from);
+                if (g > from) ++lens[l == 0 ? 0 : (l - 1) / 4];
             }
+            for (int c = 0; c < kMaxLen / 4; ++c) h_bitlens[c] = std::max(h_bitlens[c], lens[c]);
         }
         rg_off[(size_t)L.nb * (LM + 1)] = (uint32_t)L.nb * per;
         if (L.TW < L.CB) {
@@ -664,7 +666,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     v->h_csym.assign(csym, csym + n * L.WB);
     v->h_clen.assign(clen, clen + n);
     v->h_rp_off.assign(rp_off, rp_off + (size_t)L.nb * (LM + 1) + 1);
-    v->h_maxrg = h_maxrg;
+    v->h_bitlens = h_bitlens;
     v->h_maxrp.assign(LM + 1, 0);
     for (uint64_t r = 0; r < L.nb; ++r)
         for (uint32_t la = 0; la <= LM; ++la) {
@@ -851,7 +853,11 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
     P.len = D.plen;
     P.orig = D.porig;
     P.nslots = D.pslots;
-    if (probe_thr_applies(D)) {   // byte-wide score codes: selection, no lists
+    const uint64_t list_bytes = 8 * n * (uint64_t)W.cap;   // not in use yet
+    if (probe_thr_applies(D) && probe_bits_applies(D, (int)k + 1, list_bytes)) {
+        if ((e = launch_probe_bits(D, (int)k + 1, thr, lists, st)) != hipSuccess)
+            return dev_fail(e, "launching the threshold pre-pass");
+    } else if (probe_thr_applies(D)) {   // byte-wide score codes: selection, no lists
         if ((e = launch_probe_thr(D, R, v->h_gp_off.data(), (int)k + 1, thr, st)) != hipSuccess)
             return dev_fail(e, "launching the threshold pre-pass");
     } else {
@@ -877,12 +883,12 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
     T.phase_mod = kPhasePeriod;
     T.phase_lo = 0;
     T.phase_hi = 0;
-    if ((e = launch_topk_main(D, v->h_maxrg.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    if ((e = launch_topk_main(D, v->h_bitlens.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
     if ((e = launch_tighten(cnt, lists, W.cap, (int64_t)n, (int)k, thr, st)) != hipSuccess)
         return dev_fail(e, "launching the threshold update");
     T.phase_lo = 1;
     T.phase_hi = kPhasePeriod - 1;
-    if ((e = launch_topk_main(D, v->h_maxrg.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    if ((e = launch_topk_main(D, v->h_bitlens.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
     if ((e = hipEventRecord(vm->ev[2], st)) != hipSuccess) return dev_fail(e, "recording a timing event");
     // 3. the best k of each word's candidates
     if ((e = launch_select(cnt, lists, W.cap, (int64_t)n, (int)k, D.lo, d_score, d_index, ovf, reinterpret_cast<int32_t *>(ovf + 1), st)) != hipSuccess)

@@ -338,6 +338,29 @@ __device__ __forceinline__ uint32_t pair_sum(const uint32_t (&g)[P], uint32_t b)
     return x;
 }
 
+// cnt[x] += the pairs of `valid` whose sum is x, x = 0 .. GMAX: the low three
+// planes select one of eight masks, the others one function per value.
+template <int GMAX, int P>
+__device__ __forceinline__ void count_values(const uint32_t (&s)[P], uint32_t valid, uint32_t (&cnt)[GMAX + 1])
+{
+    uint32_t low[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        uint32_t m = valid;
+        if (GMAX > 0) m &= (x & 1) ? s[0] : ~s[0];
+        if (P > 1) m &= (x & 2) ? s[P > 1 ? 1 : 0] : ~s[P > 1 ? 1 : 0];
+        if (P > 2) m &= (x & 4) ? s[P > 2 ? 2 : 0] : ~s[P > 2 ? 2 : 0];
+        low[x] = m;
+    }
+#pragma unroll
+    for (int x = 0; x <= GMAX; ++x) {
+        uint32_t m = low[x & 7];
+#pragma unroll
+        for (int q = 3; q < P; ++q) m &= (x >> q & 1) ? s[q] : ~s[q];
+        cnt[x] += (uint32_t)__builtin_popcount(m);
+    }
+}
+
 // Eight planes to bytes: byte k of o[j] is the value of pair 8k + j (three
 // rounds of exchanges, each swapping half of the bits of two planes).
 __device__ __forceinline__ void planes_to_bytes(uint32_t (&p)[8])
@@ -379,6 +402,14 @@ __device__ __forceinline__ void transpose32(uint32_t (&m)[32])
 }
 
 // ---------------------------------------------------------------- LDS tables
+// LDS of a launch: `fixed` bytes and as many groups of `per` bytes as fit
+// `aim`, at least one and at most `most`; no more is asked for, so that short
+// rows get more workgroups per CU.
+__host__ __device__ constexpr uint32_t bit_lds_bytes(uint32_t fixed, uint32_t per, uint32_t aim, uint32_t most)
+{
+    const uint32_t fit = aim > fixed ? (aim - fixed) / per : 0u;
+    return fixed + per * (fit < 1u ? 1u : fit < most ? fit : most);
+}
 // One group of row words in LDS: its table, the row masks and caller indices.
 __host__ __device__ constexpr uint32_t bit_group_bytes(int LA, int tab, int alphabet)
 {
@@ -405,9 +436,9 @@ __device__ __forceinline__ BitGroup bit_group(uint8_t *base, int alphabet)
 // the workgroup call it; the caller's barrier after it completes the build.
 // It clears the tables first, so no thread may still read the old groups
 // when it is entered.
+// (build_tables: all but the caller indices.)
 template <int LA, class S, int NT, typename SlotOf>
-__device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, int n, uint8_t *lds, uint32_t stride,
-                                             SlotOf slot_of)
+__device__ __forceinline__ void build_tables(const DevVocab &V, int n, uint8_t *lds, uint32_t stride, SlotOf slot_of)
 {
     // kept from hoisting the addresses of the build over the caller's loop
     const int tid = (int)in_vgpr(threadIdx.x);
@@ -457,13 +488,6 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, int 
                 if (hf * 32 + c < A) t[(uint32_t)(hf * 32 + c) * RD + (uint32_t)(i * 3 + q)] = m[c];
         }
     }
-    for (int x = tid; x < n * kBitRows; x += NT) {
-        const int g = x >> 5, b = x & (kBitRows - 1);
-        const int64_t slot = slot_of(g, b);
-        const uint32_t col = slot >= 0 ? (uint32_t)V.bcol[slot] : 0xFFFFu;
-        BitGroup G = bit_group<LA, S>(lds + (uint32_t)g * stride, A);
-        G.cu[b] = col == 0xFFFFu ? -1 : (int32_t)(I0 + col);
-    }
     if constexpr (LA > 0) {
         // a wavefront takes two groups, a lane one row word of one of them
         const int lane = tid & 63;
@@ -485,6 +509,22 @@ __device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, int 
                 if (b + 32 < LA) rm[b + 32] = m1;
             }
         }
+    }
+}
+
+template <int LA, class S, int NT, typename SlotOf>
+__device__ __forceinline__ void build_groups(const DevVocab &V, int64_t I0, int n, uint8_t *lds, uint32_t stride,
+                                             SlotOf slot_of)
+{
+    build_tables<LA, S, NT>(V, n, lds, stride, slot_of);
+    const int tid = (int)in_vgpr(threadIdx.x);
+    const int A = V.alphabet;
+    for (int x = tid; x < n * kBitRows; x += NT) {
+        const int g = x >> 5, b = x & (kBitRows - 1);
+        const int64_t slot = slot_of(g, b);
+        const uint32_t col = slot >= 0 ? (uint32_t)V.bcol[slot] : 0xFFFFu;
+        BitGroup G = bit_group<LA, S>(lds + (uint32_t)g * stride, A);
+        G.cu[b] = col == 0xFFFFu ? -1 : (int32_t)(I0 + col);
     }
 }
 

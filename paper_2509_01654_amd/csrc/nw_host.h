@@ -36,7 +36,8 @@ struct nw_vocab {
     std::vector<uint8_t> h_clen;
     std::vector<uint32_t> h_rp_off;   // host copy of dev.rp_off
     std::vector<uint32_t> h_maxrp;    // per row length: most row pairs of that length in one block
-    std::vector<uint32_t> h_maxrg;    // per longest length: most groups of 32 row words in one block
+    // per class of four lengths: most lengths of it that one block has groups of 32 row words of
+    std::vector<uint32_t> h_bitlens;
     uint32_t h_maxdp[nw::kDiagClasses] = {};   // per anti-diagonal class: most row pairs in one block
     int32_t smin = 0, smax = 0;       // similarity extremes
     // phase timing of the last top-k call (HIP events on the caller's stream)

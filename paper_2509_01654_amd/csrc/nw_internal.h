@@ -185,6 +185,13 @@ bool probe_thr_applies(const DevVocab &V);
 hipError_t launch_probe_thr(const DevVocab &V, const RowSet &R, const uint32_t *h_off, int m, uint64_t *thr,
                             hipStream_t stream);
 
+// The same keys by the bit-plane kernels (k_probe_bits.h), for dictionaries of at
+// least kProbeBitsMinWords words that they hold; scratch is device memory of
+// scratch_bytes, 256-byte aligned, free until the pass has run.
+constexpr int64_t kProbeBitsMinWords = 131073;
+bool probe_bits_applies(const DevVocab &V, int m, uint64_t scratch_bytes);
+hipError_t launch_probe_bits(const DevVocab &V, int m, uint64_t *thr, void *scratch, hipStream_t stream);
+
 // Write recomputed lists: for t < B, the first k entries of (qs, qi)[t][0..kq)
 // whose index is not words[t] go to score/index[words[t]][0..k), padded with
 // (INT16_MIN, -1).
@@ -193,9 +200,10 @@ hipError_t launch_scatter_lists(const int16_t *qs, const int32_t *qi, const int3
 
 // Main pass of the all-pairs top-k: candidates >= thr into per-word lists,
 // plus the histogram.
-// h_maxrg[LA] (host) = most groups of 32 row words with longest length LA in one block.
+// h_bitlens[c] (host) = most lengths of class c (four each, nw_bits.h) that one
+// block has groups of 32 row words of.
 struct TopkArgs;
-hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_maxrg, const TopkArgs &T, hipStream_t stream);
+hipError_t launch_topk_main(const DevVocab &V, const uint32_t *h_bitlens, const TopkArgs &T, hipStream_t stream);
 
 // dst[0 .. bytes) (device) = src (host), carried as kernel arguments: nothing on
 // the host has to outlive the call.  For images of a few KiB.

@@ -8,6 +8,9 @@ both sides of every rule that picks 2 planes, 3 planes or the packed kernels.
 Scores are integers: no tolerance.
 """
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -189,3 +192,52 @@ def test_edges_bits(name, n, lmax):
             if count > 10:
                 i, j, s, count2 = dv.all_pairs_edges(a, b, normalised=norm, den=den, idx_begin=i0, idx_end=i1, cap=count - 7)
                 assert count2 == count and set(zip(i.tolist(), j.tolist(), s.tolist())) <= set(got)
+
+
+# name -> (generator args of test_gpu_prepass.make_vocab, k): from the size on at
+# which the bit-plane pre-pass applies; ties, empty words, odd probe counts
+PREPASS = {
+    "zipf_131073": (("zipf", 131073, 21), 32),
+    "zipf_140003": (("zipf", 140003, 22), 1),
+    "uni4_150001": (("uniform", 150001, 23, 4, 0, 12), 63),
+    "uni2_132000": (("uniform", 132000, 24, 2, 1, 9), 16),
+}
+
+PREPASS_CHILD = r"""
+import sys
+sys.path.insert(0, sys.argv[1]); sys.path.insert(0, sys.argv[1] + "/tests")
+import numpy as np
+import test_gpu_bits as T
+for name in T.PREPASS:
+    np.savez(f"{sys.argv[2]}/{name}.npz", **T.prepass_case(name))
+    print("child done", name, flush=True)
+"""
+
+
+def prepass_case(name):
+    nw, torch = _nw()
+    from test_gpu_prepass import make_vocab
+    gen, k = PREPASS[name]
+    v = make_vocab(gen)
+    alphabet = 40 if gen[0] == "zipf" else gen[3]
+    dv = nw.Vocab(v.symbols, v.offsets, nw.Scoring(alphabet, 1, -1, -1))
+    ws = torch.zeros(dv.topk_workspace_bytes(k), dtype=torch.uint8, device="cuda")
+    s, i, _ = dv.all_pairs_topk(k, hist=False, ws=ws)
+    torch.cuda.synchronize()
+    o = (8 * v.n + 255) // 256 * 256
+    a = ws[:o + 4 * v.n].cpu().numpy()
+    return dict(thr=a[:8 * v.n].view(np.uint64).copy(), cnt=a[o:].view(np.uint32).copy(), s=s.cpu().numpy(), i=i.cpu().numpy())
+
+
+def test_prepass_bits_matches_packed(tmp_path):
+    """The bit-plane pre-pass leaves the thresholds, candidate counts and lists of the packed selection."""
+    _nw()
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, NW_PREPASS="packed")
+    r = subprocess.run([sys.executable, "-c", PREPASS_CHILD, root, str(tmp_path)], env=env, capture_output=True, text=True,
+                       timeout=110)
+    assert r.returncode == 0, r.stdout + r.stderr
+    for name in PREPASS:
+        got, want = prepass_case(name), np.load(tmp_path / f"{name}.npz")
+        for key in ("thr", "cnt", "s", "i"):
+            assert np.array_equal(got[key], want[key]), (name, key, int((got[key] != want[key]).sum()))
