@@ -185,11 +185,20 @@ static int bit_wmax(const DevVocab &V) { return V.bits == 2 ? Bits2::kWmax : Bit
 // Scores (not edges) of dictionaries the bit planes hold, where the staging
 // and one group of the longest row words fit in LDS.  16-bit staging covers
 // every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
+// Three planes at up to 2,048 words past 12 symbols stay with the packed
+// kernels: a block has few groups of 32 rows there, whose tables serve few
+// columns, and what counts is the length of one workgroup.  Packed / planes,
+// int16, us: 79 / 86 at 500 words to 18 symbols, 85 / 107 to 30, 108 / 142 to
+// 42; 77 / 85, 116 / 125 and 158 / 163 at 2,000 words, 109 / 91, 204 / 138 and
+// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.
+constexpr int64_t kPlanesAboveWords = 2048;
+constexpr int kPlanesShortWords = 12;
 bool triangle_bits_applies(const DevVocab &V, int out_kind)
 {
     if (V.bits == 0 || out_kind == OUT_EDGES || packed_dp_only()) return false;
     const bool w16 = tri_bits_wide(V);
     if (w16 && V.bits == 2) return false;
+    if (V.bits == 3 && V.lmax > kPlanesShortWords && V.n <= kPlanesAboveWords) return false;
     return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16) <= kMaxLdsBytes;
 }
 

@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -75,11 +76,26 @@ int choose_block(uint64_t n, uint32_t max_len)
 }
 
 
-// Column window of the bit-plane triangle: 1024 words stage 32 rows of a byte
+// Column window of the bit-plane triangle.  1024 words stage 32 rows of a byte
 // in 32 KB of LDS, four workgroups per CU (windows of 512 words: the 50k-word
 // triangle took 0.84 ms against 0.81, a narrow chunk of a 200k-word one 0.32
-// against 0.40; before the launches were merged).
+// against 0.40; before the launches were merged).  A window is sorted by
+// length, so a wide one deals each wavefront long and short columns between
+// two barriers and pads less; a narrow one gives more workgroups.  Windows of
+// 256 / 512 / 1024 words, int16, us: 3,000 words to 24 symbols 104 / 107 /
+// 138, 4,000 words 157 / 123 / 147, 6,000 words 225 / 161 / 156, 16,384 words
+// 1157 / 836 / 534 under a matrix; 3,000 words to 18 symbols 40 / 38 / 47,
+// 6,000 words 79 / 59 / 58, 12,000 words 176 / 145 / 129 without.  Scores of
+// more than 256 values stage 64 KB and run eight wavefronts: 401 / 290 / 241
+// at 3,000 words to 48 symbols, 192 / 172 / 198 at 1,500.
 constexpr int kTriWindow = 1024;
+constexpr uint64_t kNarrowWindowWords = 3072, kHalfWindowWords = 6144, kWideScoresNarrowWords = 2048;
+int choose_window(uint64_t n, int CB, bool wide)
+{
+    if (CB >= kTriWindow) return kTriWindow;
+    if (wide) return n <= kWideScoresNarrowWords ? CB : kTriWindow;
+    return n <= kNarrowWindowWords ? CB : n <= kHalfWindowWords ? kTriWindow / 2 : kTriWindow;
+}
 
 // Probe subset of the top-k threshold pre-pass: a sixteenth of the dictionary,
 // between 1,024 and 8,192 words.  The pre-pass scores every word against every
@@ -105,7 +121,8 @@ struct Layout {
     uint64_t nprobe, pslots;
 };
 
-Layout make_layout(uint64_t n, uint32_t max_len)
+// The regions do not depend on `wide` (choose_window): only TW and nwin do.
+Layout make_layout(uint64_t n, uint32_t max_len, bool wide = false)
 {
     Layout L{};
     L.CB = choose_block(n, max_len);
@@ -143,11 +160,11 @@ Layout make_layout(uint64_t n, uint32_t max_len)
     const bool narrow = max_len <= (uint32_t)kMaxLen;
     L.rg_off = take(narrow ? ((uint64_t)L.nb * (max_len + 1) + 1) * 4 : 0);
     L.wplanes = take(narrow ? 256 * 3 * 8 * 4 : 0);
-    // the triangle's column windows: the blocks themselves up to kTriWindow words
-    L.TW = std::min(L.CB, kTriWindow);
+    // the triangle's column windows, where they are not the blocks themselves
+    L.TW = choose_window(n, L.CB, wide);
     L.nwin = (int)((n + L.TW - 1) / L.TW);
-    const bool windows = narrow && L.TW < L.CB;
-    const uint64_t tslots = windows ? (uint64_t)L.nwin * L.TW : 0;
+    const bool windows = narrow && (L.CB > kTriWindow || (L.CB < kTriWindow && n > kWideScoresNarrowWords));
+    const uint64_t tslots = windows ? (n + kTriWindow - 1) / kTriWindow * kTriWindow : 0;
     L.tlen = take(tslots);
     L.tcol = take(tslots * 2);
     L.ccol = take(narrow ? slots * kWordBytes : 0);   // from here on written on the device
@@ -417,7 +434,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         bits = plain ? 2 : 3;
     }
 
-    const Layout L = make_layout(n, max_len);
+    const Layout L = make_layout(n, max_len, hi - lo > 255);
     if (!d_mem) return fail(NW_EINVAL, "d_mem is NULL");
     if ((uintptr_t)d_mem % 256) return fail(NW_EINVAL, "d_mem must be 256-byte aligned");
     if (d_bytes < L.total)
@@ -571,7 +588,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
             for (int c = 0; c < kMaxLen / 4; ++c) h_bitlens[c] = std::max(h_bitlens[c], lens[c]);
         }
         rg_off[(size_t)L.nb * (LM + 1)] = (uint32_t)L.nb * per;
-        if (L.TW < L.CB) {
+        if (L.TW != L.CB) {
             // windows: the slots of their block in order, padding first
             uint8_t *tlen = img.data() + L.tlen;
             uint16_t *tcol = reinterpret_cast<uint16_t *>(img.data() + L.tcol);
@@ -583,7 +600,14 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
                     tcol[next[w]++] = 0xFFFF;
                 }
             }
-            for (uint64_t s = 0; s < (uint64_t)L.nb * L.CB; ++s) {
+            // a window of several blocks takes their slots sorted by length
+            // again (a counting sort; within a length in slot order)
+            std::vector<uint32_t> order((size_t)L.nb * L.CB), at(LM + 2);
+            if (L.TW > L.CB)
+                for (size_t s = 0; s < order.size(); ++s) ++at[blen[s] + 1];
+            std::partial_sum(at.begin(), at.end(), at.begin());
+            for (size_t s = 0; s < order.size(); ++s) order[L.TW > L.CB ? at[blen[s]]++ : s] = (uint32_t)s;
+            for (const uint32_t s : order) {
                 if (borig[s] < 0) continue;
                 const int w = borig[s] / L.TW;
                 tlen[next[w]] = blen[s];
@@ -650,7 +674,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     D.ccol = reinterpret_cast<const uint32_t *>(base + L.ccol);
     D.TW = L.TW;
     D.nwin = L.nwin;
-    const bool windows = L.TW < L.CB;
+    const bool windows = L.TW != L.CB;
     D.tlen = windows ? base + L.tlen : D.blen;
     D.tcol = windows ? reinterpret_cast<const uint16_t *>(base + L.tcol) : D.bcol;
     D.tccol = windows ? reinterpret_cast<const uint32_t *>(base + L.tccol) : D.ccol;

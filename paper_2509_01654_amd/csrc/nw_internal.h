@@ -86,7 +86,7 @@ struct DevVocab {
     const uint32_t *ccol;       // [nb*CB/64][12][64]
     const uint32_t *wplanes;    // [256][3][8]
     // Column windows of the bit-plane triangle: TW consecutive caller-order
-    // words (TW divides CB), sorted like a block.  Slot s (global: window *
+    // words (TW divides CB or CB divides TW), sorted like a block.  Slot s (global: window *
     // TW + local) holds word window * TW + tcol[s] (0xFFFF for padding slots,
     // first), of length tlen[s]; tccol has their words like ccol.
     int32_t TW;

@@ -172,6 +172,36 @@ def test_triangle_bits_windows(n, lmax):
 
 
 @pytest.mark.parametrize("name", list(SCORINGS))
+@pytest.mark.parametrize("n,lmax", [(2048, 13), (2049, 48), (2049, 13), (3073, 36), (6145, 25), (6145, 48)])
+def test_triangle_bits_small_windows(name, n, lmax):
+    """Blocks of 256 words with windows of 256, 512 and 1024, and the line below
+    which three planes stay with the packed kernels: ranges at every byte
+    alignment against the oracle (the whole triangle up to 2,049 words)."""
+    nw, torch = _nw()
+    v = _words(n, SCORINGS[name][0], lmax, seed=7)
+    dv, sim, gap = _load(name, v)
+    start = lambda u: u * (2 * n - u - 1) // 2
+    ranges = [(start(u) + c, start(u + 1)) for u, c in
+              [(0, 0), (255, 0), (256, 0), (511, 700), (1023, 0), (1024, 1), (n - 1025, 3), (n - 258, 0), (n - 2, 0)]]
+    ranges += [(start(250) + 9, start(262) + 1300), (start(n - 300) + 5, start(n - 200))]
+    if n <= 2049:
+        ranges.append((0, n * (n - 1) // 2))
+    whole = dv.all_pairs_scores(dtype=torch.int16)
+    for q, (a, b) in enumerate(ranges):
+        buf = torch.full(((b - a) * 2 + 16,), 0x55, dtype=torch.uint8, device="cuda:0")
+        rc = nw._lib.nw_all_pairs_scores(dv._h, a, b, 2, ctypes.c_void_p(buf.data_ptr() + q % 4),
+                                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == nw.NW_OK
+        torch.cuda.synchronize()
+        host = buf.cpu().numpy()
+        got = host[q % 4:q % 4 + (b - a) * 2].copy().view(np.int16)
+        want = oracle.triangle(v.symbols, v.offsets, sim, gap, a, b)
+        assert np.array_equal(got.astype(np.int32), want), (a, b)
+        assert np.array_equal(whole[a:b].cpu().numpy(), got), (a, b)
+        assert (host[:q % 4] == 0x55).all() and (host[q % 4 + (b - a) * 2:] == 0x55).all(), (a, b)
+
+
+@pytest.mark.parametrize("name", list(SCORINGS))
 @pytest.mark.parametrize("n,lmax", [(333, 48), (530, 11)])
 def test_edges_bits(name, n, lmax):
     """Raw and normalised slices, counting alone, a capacity below the count, ranges and a dense slice."""
