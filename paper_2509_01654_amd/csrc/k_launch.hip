@@ -185,13 +185,15 @@ static int bit_wmax(const DevVocab &V) { return V.bits == 2 ? Bits2::kWmax : Bit
 // Scores (not edges) of dictionaries the bit planes hold, where the staging
 // and one group of the longest row words fit in LDS.  16-bit staging covers
 // every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
-// Three planes at up to 2,048 words past 12 symbols stay with the packed
+// Three planes at up to 2,304 words past 12 symbols stay with the packed
 // kernels: a block has few groups of 32 rows there, whose tables serve few
 // columns, and what counts is the length of one workgroup.  Packed / planes,
 // int16, us: 79 / 86 at 500 words to 18 symbols, 85 / 107 to 30, 108 / 142 to
 // 42; 77 / 85, 116 / 125 and 158 / 163 at 2,000 words, 109 / 91, 204 / 138 and
-// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.
-constexpr int64_t kPlanesAboveWords = 2048;
+// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.  Eight dictionaries
+// in one batch, the largest of 2,200 / 2,500 words to 48 symbols: 372 / 388
+// and 427 / 412.
+constexpr int64_t kPlanesAboveWords = 2304;
 constexpr int kPlanesShortWords = 12;
 bool triangle_bits_applies(const DevVocab &V, int out_kind)
 {

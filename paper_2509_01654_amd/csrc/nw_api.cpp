@@ -89,7 +89,7 @@ int choose_block(uint64_t n, uint32_t max_len)
 // more than 256 values stage 64 KB and run eight wavefronts: 401 / 290 / 241
 // at 3,000 words to 48 symbols, 192 / 172 / 198 at 1,500.
 constexpr int kTriWindow = 1024;
-constexpr uint64_t kNarrowWindowWords = 3072, kHalfWindowWords = 6144, kWideScoresNarrowWords = 2048;
+constexpr uint64_t kNarrowWindowWords = 3072, kHalfWindowWords = 6144, kWideScoresNarrowWords = 2304;
 int choose_window(uint64_t n, int CB, bool wide)
 {
     if (CB >= kTriWindow) return kTriWindow;

@@ -172,11 +172,11 @@ def test_triangle_bits_windows(n, lmax):
 
 
 @pytest.mark.parametrize("name", list(SCORINGS))
-@pytest.mark.parametrize("n,lmax", [(2048, 13), (2049, 48), (2049, 13), (3073, 36), (6145, 25), (6145, 48)])
+@pytest.mark.parametrize("n,lmax", [(2304, 13), (2305, 48), (2305, 13), (3073, 36), (6145, 25), (6145, 48)])
 def test_triangle_bits_small_windows(name, n, lmax):
     """Blocks of 256 words with windows of 256, 512 and 1024, and the line below
     which three planes stay with the packed kernels: ranges at every byte
-    alignment against the oracle (the whole triangle up to 2,049 words)."""
+    alignment against the oracle (the whole triangle up to 2,305 words)."""
     nw, torch = _nw()
     v = _words(n, SCORINGS[name][0], lmax, seed=7)
     dv, sim, gap = _load(name, v)
@@ -184,7 +184,7 @@ def test_triangle_bits_small_windows(name, n, lmax):
     ranges = [(start(u) + c, start(u + 1)) for u, c in
               [(0, 0), (255, 0), (256, 0), (511, 700), (1023, 0), (1024, 1), (n - 1025, 3), (n - 258, 0), (n - 2, 0)]]
     ranges += [(start(250) + 9, start(262) + 1300), (start(n - 300) + 5, start(n - 200))]
-    if n <= 2049:
+    if n <= 2305:
         ranges.append((0, n * (n - 1) // 2))
     whole = dv.all_pairs_scores(dtype=torch.int16)
     for q, (a, b) in enumerate(ranges):
