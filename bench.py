@@ -26,13 +26,29 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "all-pairs NW GCUPS + pairs/s at 600k words; served query p50/p99 latency"
-# The roofline of the DP kernels.  Every cell needs one packed add and one
+# Scores are exact integers: held in bit planes (words up to 48 symbols under
+# symmetric scorings of weights 0..7), else as whole numbers in binary16 halves.
+# The roofline of the packed binary16 DP kernels.  Every cell needs one packed add and one
 # packed three-input max per two cells (two pairs share a register, one in
 # each 16-bit half), i.e. one VALU lane-instruction per cell, and nothing in
 # the recurrence can fuse the add into the max.  The ceiling is therefore the
 # VALU issue rate: 256 CUs x 64 lanes x 2.4 GHz lane-instructions/s, one cell
 # each.  `frac` is measured cells/s over that ceiling.
 PEAK_ISSUE_CELLS = 256 * 64 * 2.4e9
+# The roofline of the bit-plane kernels (csrc/nw_bits.h): a cell of 32 pairs
+# takes 7 three-input functions where every match weighs 3 and every mismatch
+# 1 (two planes), and 22 with three planes.  v_bitop3_b32 in independent chains
+# on every CU sustains 56.4e12 lane-instructions/s on this card (measured; more
+# than the 39.3e12 of the packed unit), which over the functions is the ceiling.
+BIT_FUNCTION_RATE = 56.4e12
+BIT_FUNCTIONS = {2: 7, 3: 22}
+
+
+def bit_peak(planes: int) -> float:
+    """Cells per second of the bit-plane DP at the function issue ceiling."""
+    return 32 * BIT_FUNCTION_RATE / BIT_FUNCTIONS[planes]
+
+
 # The algorithmic operation count of a cell (2 adds, 2 maxes, 1 similarity
 # lookup: Algorithm 1 with max(up, left) + p hoisted) against the nominal
 # packed 16-bit rate (256 x 64 x 2 halves x 2.4 GHz).  Reported beside the
@@ -43,12 +59,15 @@ OPS_PER_CELL = 5
 PEAK_16BIT_OPS = 256 * 64 * 2 * 2.4e9
 
 
-def roofline(cells: float, seconds: float, kernel: str, traffic=None, algorithmic_bytes=None) -> dict:
-    """The roofline record of a DP kernel pass that updates `cells` cells in `seconds`."""
+def roofline(cells: float, seconds: float, kernel: str, traffic=None, algorithmic_bytes=None, planes=0) -> dict:
+    """The roofline record of a DP kernel pass that updates `cells` cells in
+    `seconds`; planes: 2 or 3 for the bit-plane kernels, 0 for the packed ones."""
     rate = cells / seconds
-    rec = {"bound": "alu", "achieved": round(rate / 1e12, 3), "peak": round(PEAK_ISSUE_CELLS / 1e12, 3),
-           "unit": "10^12 DP cells/s (VALU issue ceiling: one packed lane-instruction per cell)",
-           "frac": round(rate / PEAK_ISSUE_CELLS, 4),
+    peak = bit_peak(planes) if planes else PEAK_ISSUE_CELLS
+    rec = {"bound": "alu", "achieved": round(rate / 1e12, 3), "peak": round(peak / 1e12, 3),
+           "unit": "10^12 DP cells/s (VALU issue ceiling: " +
+                   (f"{BIT_FUNCTIONS[planes]} functions per 32 cells)" if planes else "one packed lane-instruction per cell)"),
+           "frac": round(rate / peak, 4),
            "traffic": None if traffic is None else round(traffic),
            "kernel": kernel,
            "ops_16bit": {"ops_per_cell": OPS_PER_CELL, "achieved_Tops": round(OPS_PER_CELL * rate / 1e12, 2),
@@ -63,11 +82,11 @@ def roofline(cells: float, seconds: float, kernel: str, traffic=None, algorithmi
 # HBM bytes of the main pass from rocprofv3 FETCH_SIZE / WRITE_SIZE runs, kept in
 # this summary together with the SHA-256 of the sources the kernel was built from
 COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "topk_main_paper600k_counters.md")
-MAIN_PASS_SOURCES = ["nw_internal.h", "nw_dp.h", "nw_tile_common.h", "nw_topk.h", "k_topk.h", "k_topk_code.h", "k_query.h",
-                     "k_launch.hip", "k_inst.hip", "nw_api.cpp"]
-# the same for the 50,000-word int8 triangle (k_tri_code)
-TRI_COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "tri_code_mid50k_counters.md")
-TRI_SOURCES = ["nw_internal.h", "nw_dp.h", "nw_tile_common.h", "k_tri_tiled.h", "k_tri_code.h", "k_launch.hip", "k_inst.hip",
+MAIN_PASS_SOURCES = ["nw_internal.h", "nw_bits.h", "nw_tile_common.h", "nw_topk.h", "k_topk.h", "k_topk_bits.h",
+                     "k_launch.hip", "k_bits_inst.hip", "nw_api.cpp"]
+# the same for the 50,000-word int8 triangle (k_tri_bits)
+TRI_COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "tri_bits_mid50k_counters.md")
+TRI_SOURCES = ["nw_internal.h", "nw_bits.h", "nw_tile_common.h", "k_tri_bits.h", "k_launch.hip", "k_tri_bits_inst.hip",
                "nw_api.cpp"]
 
 
@@ -267,16 +286,17 @@ def bench_batched(args, nw, synth, torch, dev):
     return {
         "metric": METRIC, "value": round(cells / (ms / 1e3) / 1e9, 1), "unit": "GCUPS", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms, 3), "higher_is_better": True,
-        "scaling": "weak", "vs_baseline": None, "dtype": "f16", "data": "synthetic",
+        "scaling": "weak", "vs_baseline": None, "dtype": "int16", "data": "synthetic",
         "pairs_per_s": pairs / (ms / 1e3),
         "config": {"workload": "batched: 8 vocabularies 1k..100k words, uniform lengths 1..8 .. 1..48, 64-symbol "
                                "seeded symmetric matrix in [-3,3] (diag +3), gap -2, every triangle as int16",
                    "pairs": pairs, "cells": cells, "options": b.options, "items": items, "launches": launches,
                    "autotune_s": round(tune_s, 1)},
         "roofline": roofline(cells, ms / 1e3,
-                             ("k_tri_tiled / k_tri_class (every dictionary's launches"
+                             ("k_tri_bits (every dictionary's launches"
                               + (", graph replay)" if b.options["use_graph"] else ", eager on forked streams)")
-                              if b.options["class_width"] == 0 else "k_tri_persist (graph replay)")),
+                              if b.options["class_width"] == 0 else "k_tri_persist (graph replay)"),
+                             planes=3 if b.options["class_width"] == 0 else 0),
         "output_GB_per_s": round(2 * pairs / (ms / 1e3) / 1e9, 1),
         "plain_per_dictionary_ms": round(plain_ms, 3),
         "plain_gcups": round(cells / (plain_ms / 1e3) / 1e9, 1),
@@ -347,13 +367,13 @@ def bench_edges(args, nw, synth, torch, dev):
     cells, E = dv.num_cells, dv.num_pairs
     return {"metric": METRIC, "value": round(cells / (ms / 1e3) / 1e9, 1), "unit": "GCUPS", "n_gpus": 1,
             "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms, 3), "higher_is_better": True,
-            "scaling": "weak", "vs_baseline": None, "dtype": "f16", "data": "synthetic",
+            "scaling": "weak", "vs_baseline": None, "dtype": "int16", "data": "synthetic",
             "pairs_per_s": E / (ms / 1e3),
             "config": {"workload": "threshold edges, normalised weight in [60, 100], 600,000 words (Zipf-40, "
                                    "clip(Poisson 8, 1, 32), +1/-1, gap -1)", "n_words": dv.n, "pairs": E,
                        "cells": cells, "edges": total},
             "edges_per_s": total / (ms / 1e3), "edge_bytes_per_s": 10 * total / (ms / 1e3),
-            "roofline": roofline(cells, ms / 1e3, "k_edges_tiled (every LA)")}
+            "roofline": roofline(cells, ms / 1e3, "k_edges_bits (every LA)", planes=2)}
 
 
 def bench_export(args, nw, synth, torch, dev):
@@ -386,7 +406,7 @@ def bench_export(args, nw, synth, torch, dev):
     assert got[0] == E * args.steps
     return {"metric": METRIC, "value": round(cells / (ms / 1e3) / 1e9, 1), "unit": "GCUPS", "n_gpus": 1,
             "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms, 3), "higher_is_better": True,
-            "scaling": "weak", "vs_baseline": None, "dtype": "f16", "data": "synthetic",
+            "scaling": "weak", "vs_baseline": None, "dtype": "int16", "data": "synthetic",
             "pairs_per_s": E / (ms / 1e3),
             "config": {"workload": "streamed int8 triangle export to host, 600,000 words (Zipf-40, clip(Poisson 8, "
                                    "1, 32), +1/-1, gap -1), 1 GiB chunks", "n_words": dv.n, "pairs": E,
@@ -492,7 +512,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f16",
+        "dtype": "int16",
         "data": "synthetic",
         "pairs_per_s": E / (ms_per_step / 1e3),
     }
@@ -509,13 +529,13 @@ def main():
         # algorithmic bytes of the main pass: the words read once (48-byte
         # slots) and every word's top-k list written once (int16 + int32)
         alg_bytes = dv.n * 48 + dv.n * k * 6
-        rec["roofline"] = roofline(cells, main_ms / 1e3, "k_topk_code (all-pairs main pass, every LA)",
-                                   None if tr is None else tr[0] + tr[1], alg_bytes)
+        rec["roofline"] = roofline(cells, main_ms / 1e3, "k_topk_bits (all-pairs main pass, every class)",
+                                   None if tr is None else tr[0] + tr[1], alg_bytes, planes=2)
         rate = measured_packed_peak(nw, torch)
-        rec["roofline"]["measured_peak"] = {
-            "kernel": "k_packed_rate (nw_packed_issue_rate: the DP's packed add + max3, independent chains)",
-            "cells_per_s": round(rate / 1e12, 3), "unit": "10^12 packed lane-instructions (= cells) per s",
-            "frac": round(cells / (main_ms / 1e3) / rate, 4)}
+        rec["roofline"]["packed_peak"] = {
+            "kernel": "k_packed_rate (nw_packed_issue_rate: the packed DP's add + max3, independent chains)",
+            "cells_per_s": round(rate / 1e12, 3), "unit": "10^12 packed lane-instructions (= cells of the packed DP) per s",
+            "note": "the packed kernels' measured ceiling; the bit planes pass it"}
         iss = counter_issue()
         if iss is not None:
             rec["roofline"]["counters"] = iss
@@ -540,8 +560,8 @@ def main():
                                      "+1/-1, gap -1)", "n_words": dv.n, "pairs": E, "cells": cells}
         tr = counter_traffic(TRI_COUNTER_SUMMARY, TRI_SOURCES) if args.workload == "mid" else None
         # algorithmic bytes: one int8 score written per pair, the words read once
-        rec["roofline"] = roofline(cells, ms_per_step / 1e3, "k_tri_code (every LA)",
-                                   None if tr is None else tr[0] + tr[1], E + dv.n * 48)
+        rec["roofline"] = roofline(cells, ms_per_step / 1e3, "k_tri_bits (every LA)",
+                                   None if tr is None else tr[0] + tr[1], E + dv.n * 48, planes=2)
         if tr is not None:
             # algorithmic bytes: one int8 score written per pair; the words read are ~1 MB
             rec["roofline"]["traffic_detail"] = {

@@ -403,13 +403,13 @@ int64_t nw_clock_ns(void);
  * Persistent form: work items (dictionary, block pair, row length, chunk of
  * row pairs) are ordered heaviest first inside row-length classes; one
  * persistent kernel per class drains its queue.  Tiled form (class_width 0):
- * every dictionary's per-length tiled launches, as nw_all_pairs_scores issues
+ * every dictionary's own launches, as nw_all_pairs_scores issues
  * them, spread over concurrent chains (library streams when eager, chains of
  * kernel nodes in the graph).  nw_batch_autotune times both.
  * ------------------------------------------------------------------------- */
 typedef struct {
     uint32_t class_width;     /* 1: one persistent kernel per row length; 8: classes of 8 lengths;
-                                 0: no persistent kernels -- every dictionary's per-length tiled
+                                 0: no persistent kernels -- every dictionary's own
                                  launches, spread over concurrent chains (wg_per_cu and
                                  pairs_per_item unused) */
     uint32_t wg_per_cu;       /* persistent workgroups per compute unit (>= 1) */

@@ -27,9 +27,10 @@
 //   to the LDS copies once per column step; otherwise the planes are turned
 //   to bytes and every pair adds to its bin.
 //
-// Bound: vector issue.  For rows and columns of 8 symbols a step of 32 x 64
-// pairs takes about 390 lane-instructions of DP, 25 of sums, 25 of tests and
-// 60 of histogram: 0.25 per cell, where the packed form takes 1.18.
+// Bound: vector issue.  The DP's functions are 0.22 lane-instructions per cell;
+// counted over the 600,000-word main pass, with columns run past a lane's own
+// word, short rows, sums, tests and histogram, 0.32, where the packed form
+// takes 1.18: 409 -> 82 ms.
 #pragma once
 
 #include "k_topk.h"
