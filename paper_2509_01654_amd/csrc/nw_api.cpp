@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -194,25 +195,51 @@ struct TopkWs {
     uint32_t cap;
 };
 
-uint32_t topk_cap(uint64_t n, uint64_t CB, uint32_t k)
+// Expected candidates of one word.  The probe threshold is the (k+1)-th best
+// key over M probe words and ranks about all = (k+1)(n-1)/M among the n-1
+// partners.  The first phase meets the share f of the partners in the block
+// columns of its period and appends about first = f * all of them.
+struct TopkExpect {
+    double f, all, first;
+    // A word with at least k candidates of the first phase has its threshold
+    // raised to their k-th best.  Below an expectation of 3 k some have fewer.
+    bool raised(uint32_t k) const { return first >= 3.0 * k; }
+};
+TopkExpect topk_expect(uint64_t n, uint64_t CB, uint32_t k)
 {
-    // Expected candidates of one word.  The probe threshold is the (k+1)-th
-    // best key over M probe words and ranks about all = (k+1)(n-1)/M among
-    // the n-1 partners.  The first phase meets the share f of the partners in
-    // the block columns of its period and appends about f * all of them.  A
-    // word with at least k has its threshold raised to their k-th best, which
-    // ranks about k/f overall, and the second phase appends fewer than that;
-    // otherwise the probe threshold stays and it appends up to `all` (counted
-    // as the rule below 3 k first candidates: some words then have fewer than
-    // k).  Twice the sum, plus a margin, bounds the list in practice; a word
-    // past the capacity is recomputed exactly.
     const uint64_t M = num_probes(n);
     const uint64_t nb = std::max<uint64_t>(1, (n + CB - 1) / CB);
-    const double f = std::min(1.0, (double)((nb + kPhasePeriod - 1) / kPhasePeriod) / (double)nb);
-    const double all = M >= n ? (double)(k + 1) : (double)(k + 1) * (double)(n - 1) / (double)M;
-    const double first = f * all;
-    const double mean = first >= 3.0 * k ? first + (double)k / f : all;
-    uint64_t cap = (uint64_t)(2.0 * mean) + 64;
+    TopkExpect x;
+    x.f = std::min(1.0, (double)((nb + kPhasePeriod - 1) / kPhasePeriod) / (double)nb);
+    x.all = M >= n ? (double)(k + 1) : (double)(k + 1) * (double)(n - 1) / (double)M;
+    x.first = x.f * x.all;
+    return x;
+}
+
+// One phase instead of two where few thresholds would be raised after the
+// first: the first phase is an eighth of the work in its own launches, too few
+// workgroups for the chip while a block has 256 words, and too few of the long
+// ones under three planes.  Two phases / one, us: 5,000 words top-16 331 / 252,
+// 8,000 words under a matrix to 31 symbols top-32 918 / 776, 30,000 words 3771
+// / 3397, 40,000 words to 16 symbols 2580 / 2272.  With two planes past 16,384
+// words the second phase's fewer candidates weigh as much: 20,000 words 649 /
+// 598 (top-16) but 889 / 925 (top-32 with histogram), 100,000 words 4831 / 4936.
+bool topk_one_phase(const DevVocab &D, uint32_t k)
+{
+    return !topk_expect((uint64_t)D.n, (uint64_t)D.CB, k).raised(k) && (D.CB == 256 || D.bits == 3);
+}
+
+uint32_t topk_cap(uint64_t n, uint64_t CB, uint32_t k)
+{
+    // A word with a raised threshold ranks about k/f overall, and the second
+    // phase appends fewer than that; otherwise the probe threshold stays and
+    // the word appends up to `all`, which spreads like a sum of k + 1 gaps:
+    // seven deviations past the mean.  Twice the mean, plus a margin, bounds
+    // the list in practice; a word past the capacity is recomputed exactly.
+    const TopkExpect x = topk_expect(n, CB, k);
+    const double most_of = x.raised(k) ? 2.0 * (x.first + (double)k / x.f)
+                                       : x.all * std::max(2.0, 1.0 + 7.0 / std::sqrt((double)k + 1.0));
+    uint64_t cap = (uint64_t)most_of + 64;
     cap = (cap + 63) / 64 * 64;
     const uint64_t most = (n + 63) / 64 * 64;
     cap = std::max<uint64_t>(64, std::min(cap, most));
@@ -895,7 +922,8 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
     // Two phases: block pairs with (b - r) mod 8 == 0 first -- every word meets
     // an eighth of its partners, spread over the whole dictionary -- then each
     // word's threshold is raised to the k-th best of its candidates so far,
-    // and the remaining block pairs emit far fewer candidates.
+    // and the remaining block pairs emit far fewer candidates.  One phase
+    // (every block pair) where that does not pay (topk_one_phase).
     TopkArgs T{};
     T.thr = thr;
     T.cnt = cnt;
@@ -904,15 +932,18 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
     T.hist = reinterpret_cast<unsigned long long *>(d_hist);
     T.lo = D.lo;
     T.nbins = nbins;
+    const bool one = topk_one_phase(D, k);
     T.phase_mod = kPhasePeriod;
     T.phase_lo = 0;
-    T.phase_hi = 0;
+    T.phase_hi = one ? kPhasePeriod - 1 : 0;
     if ((e = launch_topk_main(D, v->h_bitlens.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
-    if ((e = launch_tighten(cnt, lists, W.cap, (int64_t)n, (int)k, thr, st)) != hipSuccess)
-        return dev_fail(e, "launching the threshold update");
-    T.phase_lo = 1;
-    T.phase_hi = kPhasePeriod - 1;
-    if ((e = launch_topk_main(D, v->h_bitlens.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    if (!one) {
+        if ((e = launch_tighten(cnt, lists, W.cap, (int64_t)n, (int)k, thr, st)) != hipSuccess)
+            return dev_fail(e, "launching the threshold update");
+        T.phase_lo = 1;
+        T.phase_hi = kPhasePeriod - 1;
+        if ((e = launch_topk_main(D, v->h_bitlens.data(), T, st)) != hipSuccess) return dev_fail(e, "launching the top-k main pass");
+    }
     if ((e = hipEventRecord(vm->ev[2], st)) != hipSuccess) return dev_fail(e, "recording a timing event");
     // 3. the best k of each word's candidates
     if ((e = launch_select(cnt, lists, W.cap, (int64_t)n, (int)k, D.lo, d_score, d_index, ovf, reinterpret_cast<int32_t *>(ovf + 1), st)) != hipSuccess)

@@ -271,3 +271,21 @@ def test_prepass_bits_matches_packed(tmp_path):
         got, want = prepass_case(name), np.load(tmp_path / f"{name}.npz")
         for key in ("thr", "cnt", "s", "i"):
             assert np.array_equal(got[key], want[key]), (name, key, int((got[key] != want[key]).sum()))
+
+
+@pytest.mark.parametrize("name,n,lmax,k", [
+    ("plain", 16384, 12, 3), ("plain", 16385, 12, 3), ("plain", 5000, 12, 2), ("levenshtein", 5000, 9, 63),
+    ("levenshtein", 17000, 9, 16), ("matrix_64", 17000, 14, 1), ("weight_8", 3000, 20, 8)])
+def test_topk_phases(name, n, lmax, k):
+    """Both sides of the rule for one main-pass phase: sampled rows and the whole histogram's count."""
+    _, torch = _nw()
+    v = _words(n, SCORINGS[name][0], lmax, seed=11)
+    dv, sim, gap = _load(name, v)
+    sc, ix, h = dv.all_pairs_topk(k)
+    torch.cuda.synchronize()
+    assert int(h.sum()) == n * (n - 1) // 2
+    for r0 in (0, 255, n // 2, n - 40):
+        r1 = min(n, r0 + 40)
+        ws, wi, _ = oracle.topk_rows(v.symbols, v.offsets, sim, gap, k, r0=r0, r1=r1)
+        assert np.array_equal(sc.cpu().numpy()[r0:r1].astype(np.int32), ws)
+        assert np.array_equal(ix.cpu().numpy()[r0:r1], wi)
