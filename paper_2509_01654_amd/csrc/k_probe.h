@@ -2,7 +2,7 @@
 //
 // Every word u needs one key from the pre-pass: its key of rank m = k + 1
 // (rank 1 is the best) against the probe subset, the M words at caller
-// indices floor(i n / M), i = 0 .. M-1 (keys as in nw_topk.h: score
+// indices probe_word(i), i = 0 .. M-1 (keys as in nw_topk.h: score
 // descending, then index ascending; the word itself counts when it is a
 // probe).  When every score code s - lo fits in a byte below 0xFF, a
 // workgroup finds that key for a pair of equal-length words without keeping
@@ -14,7 +14,7 @@
 //   2. one wavefront per word walks the histogram from the best code down to
 //      the code c that holds rank m, and the place r of the wanted key among
 //      the keys of code c;
-//   3. keys of equal score rank by index ascending and floor(i n / M) rises
+//   3. keys of equal score rank by index ascending and probe_word(i) rises
 //      with i, so the wanted probe is the r-th rank i (ascending) whose code
 //      is c: a scan of the byte array, 256 ranks a step.
 // A word with fewer than m probe keys gets key 0, as a short list would.
@@ -114,7 +114,7 @@ __device__ uint64_t probe_select(uint32_t *hist, const uint8_t *codes, int64_t n
         for (uint32_t q = excl + 1; here && q < need; ++q) zz &= zz - 1u;
         const int byte = here ? (int)(__builtin_ctz(zz) >> 3) : 0;
         const int64_t i = base + 4 * W + __builtin_amdgcn_readlane(byte, W);
-        const uint64_t j = (uint64_t)i * (uint64_t)Q.n / (uint64_t)Q.nprobe;
+        const uint64_t j = probe_word((uint64_t)i, (uint64_t)Q.n, (uint64_t)Q.nprobe);
         return ((uint64_t)(uint32_t)c << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
     }
     return 0;   // not reached: the histogram counted at least r codes c

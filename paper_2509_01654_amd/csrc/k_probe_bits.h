@@ -6,7 +6,7 @@
 // after the DP is the lane's own:
 //   0. k_probe_tables builds the symbol tables of the probes' groups once, in
 //      scratch memory: set A in length order (the probe slots), set B in rank
-//      order (probe i = word floor(i n / M));
+//      order (probe i = word probe_word(i));
 //   1. k_probe_bits runs set A: every probe's score adds to the lane's
 //      histogram in LDS (16-bit counts, two to a dword, so the 64 lanes of an
 //      add hit 64 banks);
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kThreads) void k_probe_tables(DevVocab V, ProbeBits
     auto slot_of = [&](int, int b) -> int64_t {
         const int64_t i = (int64_t)g0 * kBitRows + b;
         if (!setb) return i >= (int64_t)Q.npad ? i : -1;
-        return i < V.nprobe ? i * V.n / V.nprobe : -1;
+        return i < V.nprobe ? (int64_t)probe_word((uint64_t)i, (uint64_t)V.n, (uint64_t)V.nprobe) : -1;
     };
     const int b = threadIdx.x & 31;
     const int64_t s = slot_of(0, b);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
         [&] { return __syncthreads_or(need != 0) != 0; });
 
     if (u >= 0) {
-        const uint64_t j = (uint64_t)rank * (uint64_t)V.n / (uint64_t)V.nprobe;
+        const uint64_t j = probe_word(rank, (uint64_t)V.n, (uint64_t)V.nprobe);
         Q.thr[u] = found_code ? ((uint64_t)(uint32_t)c << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j) : 0;
     }
 }

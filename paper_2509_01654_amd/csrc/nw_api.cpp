@@ -581,16 +581,16 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         h_gp_off[kMaxLen + 1] = g;
         std::memcpy(gp_off, h_gp_off.data(), (kMaxLen + 2) * 4);
     }
-    // probe subset: caller indices floor(i*n/M), sorted by length, padding slots first
+    // probe subset: caller indices probe_word(i), sorted by length, padding slots first
     {
-        // (length, rank i); u = floor(i n / M) rises with i, so this is (length, u)
+        // (length, rank i); probe_word rises with i, so this is (length, u)
         std::vector<std::pair<int, int64_t>> pr;
-        for (uint64_t i = 0; i < L.nprobe; ++i) pr.push_back({clen[i * n / L.nprobe], (int64_t)i});
+        for (uint64_t i = 0; i < L.nprobe; ++i) pr.push_back({clen[probe_word(i, n, L.nprobe)], (int64_t)i});
         std::stable_sort(pr.begin(), pr.end());
         uint64_t s = 0;
         for (; s < L.pslots - L.nprobe; ++s) { plen[s] = 0; porig[s] = -1; prank[s] = 0; }
         for (auto &e : pr) {
-            const int64_t u = (int64_t)((uint64_t)e.second * n / L.nprobe);
+            const int64_t u = (int64_t)probe_word((uint64_t)e.second, n, L.nprobe);
             plen[s] = (uint8_t)e.first;
             porig[s] = (int32_t)u;
             prank[s] = (uint16_t)e.second;
