@@ -104,10 +104,13 @@ int choose_window(uint64_t n, int CB, bool wide)
 // so fewer candidates.  With 8,192 / a quarter / an eighth / a sixteenth: 20k
 // words top-16 0.99 / 0.85 / 0.71 / 0.62 ms, 30k words with a matrix top-32
 // 5.6 / 5.6 / 4.6 / 4.1 ms, 100k words top-32 6.8 / 6.8 / 6.8 / 6.2 ms.
-constexpr uint64_t kMinProbes = 1024, kMaxProbes = 8192, kProbeShare = 16;
-uint64_t num_probes(uint64_t n)
+// The packed main pass pays more for a candidate: an eighth (a sixteenth / an
+// eighth / 8,192 in two phases, words to 12 symbols, ms: 17,000 words top-16
+// 2.24 / 1.18 / 1.94, 16,384 words top-63 1.78 / 1.23 / 1.40).
+constexpr uint64_t kMinProbes = 1024, kMaxProbes = 8192, kPlanesShare = 16, kPackedShare = 8;
+uint64_t num_probes(uint64_t n, bool planes)
 {
-    return std::min(n, std::min(kMaxProbes, std::max(kMinProbes, n / kProbeShare)));
+    return std::min(n, std::min(kMaxProbes, std::max(kMinProbes, n / (planes ? kPlanesShare : kPackedShare))));
 }
 // The first phase of the top-k main pass takes the block pairs (r, b) with
 // (b - r) mod kPhasePeriod == 0.
@@ -122,8 +125,9 @@ struct Layout {
     uint64_t nprobe, pslots;
 };
 
-// The regions do not depend on `wide` (choose_window): only TW and nwin do.
-Layout make_layout(uint64_t n, uint32_t max_len, bool wide = false)
+// The regions do not depend on `planes` (num_probes) and `wide` (choose_window):
+// only nprobe, pslots, TW and nwin do.
+Layout make_layout(uint64_t n, uint32_t max_len, bool planes = true, bool wide = false)
 {
     Layout L{};
     L.CB = choose_block(n, max_len);
@@ -151,12 +155,13 @@ Layout make_layout(uint64_t n, uint32_t max_len, bool wide = false)
     L.borig = take(slots * 4);
     L.gpairs = take(slots * 2 * 4);
     L.gp_off = take((kMaxLen + 2) * 4);
-    L.nprobe = num_probes(n);
+    L.nprobe = num_probes(n, planes);
     L.pslots = (L.nprobe + kThreads - 1) / kThreads * kThreads;
-    L.psym = take(L.pslots * L.WB);
-    L.plen = take(L.pslots);
-    L.porig = take(L.pslots * 4);
-    L.prank = take(L.pslots * 2);
+    const uint64_t room = (num_probes(n, false) + kThreads - 1) / kThreads * kThreads;   // the larger of the two
+    L.psym = take(room * L.WB);
+    L.plen = take(room);
+    L.porig = take(room * 4);
+    L.prank = take(room * 2);
     // the bit-plane kernels' arrays (words of at most kMaxLen symbols)
     const bool narrow = max_len <= (uint32_t)kMaxLen;
     L.rg_off = take(narrow ? ((uint64_t)L.nb * (max_len + 1) + 1) * 4 : 0);
@@ -205,9 +210,9 @@ struct TopkExpect {
     // raised to their k-th best.  Below an expectation of 3 k some have fewer.
     bool raised(uint32_t k) const { return first >= 3.0 * k; }
 };
-TopkExpect topk_expect(uint64_t n, uint64_t CB, uint32_t k)
+TopkExpect topk_expect(const DevVocab &D, uint32_t k)
 {
-    const uint64_t M = num_probes(n);
+    const uint64_t n = (uint64_t)D.n, CB = (uint64_t)D.CB, M = (uint64_t)D.nprobe;
     const uint64_t nb = std::max<uint64_t>(1, (n + CB - 1) / CB);
     TopkExpect x;
     x.f = std::min(1.0, (double)((nb + kPhasePeriod - 1) / kPhasePeriod) / (double)nb);
@@ -219,29 +224,31 @@ TopkExpect topk_expect(uint64_t n, uint64_t CB, uint32_t k)
 // One phase instead of two where few thresholds would be raised after the
 // first: the first phase is an eighth of the work in its own launches, too few
 // workgroups for the chip while a block has 256 words, and too few of the long
-// ones under three planes.  Two phases / one, us: 5,000 words top-16 331 / 252,
-// 8,000 words under a matrix to 31 symbols top-32 918 / 776, 30,000 words 3771
-// / 3397, 40,000 words to 16 symbols 2580 / 2272.  With two planes past 16,384
-// words the second phase's fewer candidates weigh as much: 20,000 words 649 /
-// 598 (top-16) but 889 / 925 (top-32 with histogram), 100,000 words 4831 / 4936.
+// ones under three planes or packed.  Two phases / one, us: 5,000 words top-16
+// 331 / 252, 8,000 words under a matrix to 31 symbols top-32 918 / 776, 30,000
+// words 3771 / 3397, 40,000 words to 16 symbols 2580 / 2272; packed, words to 12
+// symbols, 17,000 words top-63 3546 / 2522, 34,000 words top-32 7600 / 4949.
+// With two planes past 16,384 words the second phase's fewer candidates weigh as
+// much: 20,000 words 649 / 598 (top-16) but 889 / 925 (top-32 with histogram),
+// 100,000 words 4831 / 4936.
 bool topk_one_phase(const DevVocab &D, uint32_t k)
 {
-    return !topk_expect((uint64_t)D.n, (uint64_t)D.CB, k).raised(k) && (D.CB == 256 || D.bits == 3);
+    return !topk_expect(D, k).raised(k) && (D.CB == 256 || D.bits != 2);
 }
 
-uint32_t topk_cap(uint64_t n, uint64_t CB, uint32_t k)
+uint32_t topk_cap(const DevVocab &D, uint32_t k)
 {
     // A word with a raised threshold ranks about k/f overall, and the second
     // phase appends fewer than that; otherwise the probe threshold stays and
     // the word appends up to `all`, which spreads like a sum of k + 1 gaps:
     // seven deviations past the mean.  Twice the mean, plus a margin, bounds
     // the list in practice; a word past the capacity is recomputed exactly.
-    const TopkExpect x = topk_expect(n, CB, k);
+    const TopkExpect x = topk_expect(D, k);
     const double most_of = x.raised(k) ? 2.0 * (x.first + (double)k / x.f)
                                        : x.all * std::max(2.0, 1.0 + 7.0 / std::sqrt((double)k + 1.0));
     uint64_t cap = (uint64_t)most_of + 64;
     cap = (cap + 63) / 64 * 64;
-    const uint64_t most = (n + 63) / 64 * 64;
+    const uint64_t most = ((uint64_t)D.n + 63) / 64 * 64;
     cap = std::max<uint64_t>(64, std::min(cap, most));
     // NW_TOPK_CAP overrides the capacity (tests use it to force the
     // overflow recomputation)
@@ -254,10 +261,11 @@ uint32_t topk_cap(uint64_t n, uint64_t CB, uint32_t k)
 
 // lists_prepass: the pre-pass keeps wave lists (wide score codes), which need
 // the partial area; the selection pre-pass writes the thresholds directly.
-TopkWs topk_ws(uint64_t n, uint64_t CB, uint32_t k, bool lists_prepass)
+TopkWs topk_ws(const DevVocab &D, uint32_t k, bool lists_prepass)
 {
     TopkWs w{};
-    w.cap = topk_cap(n, CB, k);
+    const uint64_t n = (uint64_t)D.n;
+    w.cap = topk_cap(D, k);
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) {
         uint64_t at = o;
@@ -461,7 +469,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         bits = plain ? 2 : 3;
     }
 
-    const Layout L = make_layout(n, max_len, hi - lo > 255);
+    const Layout L = make_layout(n, max_len, bits != 0, hi - lo > 255);
     if (!d_mem) return fail(NW_EINVAL, "d_mem is NULL");
     if ((uintptr_t)d_mem % 256) return fail(NW_EINVAL, "d_mem must be 256-byte aligned");
     if (d_bytes < L.total)
@@ -844,7 +852,7 @@ int nw_topk_workspace_bytes(const nw_vocab *v, uint32_t k, uint64_t *bytes)
 {
     if (!v || !bytes) return fail(NW_EINVAL, "NULL argument");
     if (k < 1 || k > 63) return fail(NW_EINVAL, "k = %u outside 1..63", k);
-    *bytes = topk_ws(v->n, (uint64_t)v->dev.CB, k, !probe_thr_applies(v->dev)).total;
+    *bytes = topk_ws(v->dev, k, !probe_thr_applies(v->dev)).total;
     return ok();
 }
 
@@ -859,7 +867,7 @@ int check_topk_args(const nw_vocab *v, uint32_t k, const int16_t *d_score, const
     if (!v->symmetric) return fail(NW_EINVAL, "all-pairs scoring needs a symmetric similarity matrix");
     if (v->max_len > (uint32_t)kMaxLen)
         return fail(NW_EINVAL, "top-k supports words of at most %d symbols (this dictionary has %u)", kMaxLen, v->max_len);
-    const TopkWs W = topk_ws(v->n, (uint64_t)v->dev.CB, k, !probe_thr_applies(v->dev));
+    const TopkWs W = topk_ws(v->dev, k, !probe_thr_applies(v->dev));
     if (v->n > 0 && (!d_score || !d_index)) return fail(NW_EINVAL, "d_score / d_index is NULL");
     if (!d_ws || (uintptr_t)d_ws % 256) return fail(NW_EINVAL, "d_ws must be a 256-byte aligned device pointer");
     if (ws_bytes < W.total)
@@ -874,7 +882,7 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
                  hipStream_t st)
 {
     const uint64_t n = v->n;
-    const TopkWs W = topk_ws(n, (uint64_t)v->dev.CB, k, !probe_thr_applies(v->dev));
+    const TopkWs W = topk_ws(v->dev, k, !probe_thr_applies(v->dev));
     const DevVocab &D = v->dev;
     const int nbins = v->hi - v->lo + 1;
     uint8_t *ws = static_cast<uint8_t *>(d_ws);
@@ -958,7 +966,7 @@ int topk_enqueue(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_ind
 int topk_finish(const nw_vocab *v, uint32_t k, int16_t *d_score, int32_t *d_index, void *d_ws, hipStream_t st)
 {
     const uint64_t n = v->n;
-    const TopkWs W = topk_ws(n, (uint64_t)v->dev.CB, k, !probe_thr_applies(v->dev));
+    const TopkWs W = topk_ws(v->dev, k, !probe_thr_applies(v->dev));
     nw_vocab *vm = const_cast<nw_vocab *>(v);
     const DevVocab &D = v->dev;
     uint8_t *ws = static_cast<uint8_t *>(d_ws);

@@ -1,0 +1,103 @@
+"""What the calls launch, on the CPU: a preloaded HIP runtime (hip_recorder.c)
+records kernels, grids and streams and runs nothing, so the host's rules -- which
+kernel a dictionary takes, how a launch is cut, on which stream it goes -- are
+tested where there is no GPU.  Every check runs in one child process per group.
+"""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests")
+
+
+class _Record(ctypes.Structure):
+    _fields_ = [("name", ctypes.c_char * 512), ("grid", ctypes.c_uint32 * 3), ("block", ctypes.c_uint32 * 3),
+                ("lds", ctypes.c_uint64), ("stream", ctypes.c_uint64)]
+
+
+class Recorder:
+    """The recorder and libnw in this (child) process."""
+
+    def __init__(self):
+        import paper_2509_01654_amd as nw
+        self.nw, self.lib = nw, nw.load_library()
+        self.hip = ctypes.CDLL(None)
+        self.hip.rec_get.restype = ctypes.POINTER(_Record)
+        self.P = ctypes.c_void_p
+
+    def load(self, symbols, offsets, sc):
+        symbols = np.ascontiguousarray(symbols, dtype=np.uint8)
+        offsets = np.ascontiguousarray(offsets, dtype=np.uint64)
+        h = ctypes.c_void_p()
+        c = sc._c()
+        rc = self.lib.nw_load_vocab(symbols.ctypes.data, offsets.ctypes.data, offsets.shape[0] - 1, ctypes.byref(c),
+                                    self.P(1 << 40), 1 << 40, None, ctypes.byref(h))
+        assert rc == 0, self.lib.nw_last_error()
+        return h
+
+    def launches(self, fn, *args):
+        """[(kernel, grid, threads, lds, stream)] of one call."""
+        self.hip.rec_clear()
+        rc = fn(*args)
+        assert rc == 0, self.lib.nw_last_error()
+        out = []
+        for i in range(self.hip.rec_count()):
+            r = self.hip.rec_get(i).contents
+            out.append((r.name.decode(), tuple(r.grid), r.block[0], r.lds, r.stream))
+        return out
+
+
+def words(n, alphabet, lo, hi, seed=5):
+    rng = np.random.default_rng(seed)
+    lengths = rng.integers(lo, hi + 1, size=n)
+    offsets = np.zeros(n + 1, np.uint64)
+    np.cumsum(lengths, out=offsets[1:])
+    return rng.integers(0, alphabet, size=int(lengths.sum())), offsets
+
+
+@pytest.fixture(scope="module")
+def recorder_library(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("recorder") / "hip_recorder.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_recorder.c"), "-ldl"], check=True)
+    return so
+
+
+def _child(recorder_library, check):
+    """Run check_<name>(Recorder) in a child with the recorder preloaded."""
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = recorder_library + (":" + env["LD_PRELOAD"] if env.get("LD_PRELOAD") else "")
+    code = (f"import sys; sys.path[:0] = [{ROOT!r}, {HERE!r}]\n"
+            f"import test_launches as T\nT.{check}(T.Recorder())\nprint('checked')\n")
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "checked" in r.stdout, r.stdout[-3000:] + r.stderr[-3000:]
+
+
+def _topk_bytes(R, h, k):
+    out = ctypes.c_uint64()
+    assert R.lib.nw_topk_workspace_bytes(h, k, ctypes.byref(out)) == 0
+    return out.value
+
+
+def check_packed_topk(R):
+    # 17,000 words, one of eight a probe: about 8 (k + 1) candidates of a word,
+    # twice that as its list (a sixteenth: 16 (k + 1))
+    n, k = 17000, 63
+    h = R.load(*words(n, 40, 0, 12), R.nw.Scoring(40, 4, -1, -2))
+    need = _topk_bytes(R, h, k)
+    assert need < 8 * n * (2.5 * 8 * (k + 1))
+    # and no first phase of its own: too few words would get a closer threshold
+    P = R.P
+    for k in (16, 63):
+        names = [x[0] for x in R.launches(R.lib.nw_all_pairs_topk_async, h, k, P(1 << 41), P(1 << 42), None, P(1 << 43),
+                                          _topk_bytes(R, h, k), None)]
+        assert any("k_topk_code" in x for x in names) and not any("tighten" in x for x in names), names
+
+
+def test_packed_topk_thresholds(recorder_library):
+    """The packed main pass pays more for a candidate than the plane kernels do."""
+    _child(recorder_library, "check_packed_topk")
