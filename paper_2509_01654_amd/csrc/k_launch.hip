@@ -379,7 +379,7 @@ static int col_splits(uint64_t tiles, int CB)
 
 static bool edges_bits_applies(const DevVocab &V)
 {
-    return V.bits != 0 && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V) <= kMaxLdsBytes;
+    return V.bits != 0 && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, 1) <= kMaxLdsBytes;
 }
 
 hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
@@ -395,14 +395,21 @@ hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64
         for (const LengthRange &L : bits_launches(V, h_maxrp)) {
             DevVocab Vc = V;
             EdgeSink Ec = E;
-            uint64_t ib = idx_begin, ie = idx_end;
-            uint32_t rb0 = G.rb0, rbn = G.rbn;
-            int splits = col_splits(G.blocks, V.CB), hi = L.hi;
-            uint32_t lds = edges_bits_lds_bytes(hi, bit_tab(V), bit_wmax(V), V);
-            void *args[] = {&Vc, &Ec, &ib, &ie, &rb0, &rbn, &splits, &hi, &lds};
+            EdgeRange X;
+            X.idx_begin = idx_begin;
+            X.idx_end = idx_end;
+            X.row0 = (int32_t)row_of_index(V.n, idx_begin);
+            X.row1 = (int32_t)row_of_index(V.n, idx_end - 1);
+            X.rb0 = G.rb0;
+            X.rbn = G.rbn;
+            X.splits = col_splits(G.blocks, V.CB);
+            X.hi = L.hi;
+            X.most = kBitMaxGroups;
+            uint32_t lds = edges_bits_lds_bytes(L.hi, bit_tab(V), bit_wmax(V), V, X.most);
+            void *args[] = {&Vc, &Ec, &X, &lds};
             hipError_t e = launch_dyn(tab.edges_bits[V.bits - 2][L.range],
-                                      dim3((uint32_t)((uint64_t)G.blocks * splits), (uint32_t)(L.hi - L.lo + 1)), lds,
-                                      fork, args);
+                                      dim3((uint32_t)((uint64_t)G.blocks * X.splits), (uint32_t)(L.hi - L.lo + 1), 1), lds, fork,
+                                      args);
             if (e != hipSuccess) return e;
         }
         return fork.end();
