@@ -377,6 +377,34 @@ static int col_splits(uint64_t tiles, int CB)
     return s;
 }
 
+// How many row groups a workgroup of the edge emitter takes at a time (most), and
+// over how many workgroups a tile's groups of one length are dealt (parts).  With
+// all of them in turn, a tile of a dictionary of few lengths is one long chain
+// while the chip idles: below kEnough workgroups they are dealt, down to one group
+// each.  Words of one length, packed / a workgroup a tile / dealt, us: 2,300 words
+// of 24 symbols under a matrix 320 / 516 / 168, 700 words of 48 symbols 275 / 471
+// / 107.
+static void bits_parts(const DevVocab &V, const uint32_t *h_maxrp, const LengthRange &L, uint64_t tiles, int &most,
+                       uint32_t &parts)
+{
+    constexpr uint64_t kEnough = 2048;
+    uint32_t lengths = 0, groups = 1;
+    for (int LA = L.lo; LA <= L.hi; ++LA) {
+        lengths += h_maxrp[LA] != 0;
+        // groups with their longest word of length LA: its words, and up to a
+        // group's worth of shorter ones
+        if (h_maxrp[LA]) groups = std::max(groups, h_maxrp[LA] * 2 / kBitRows + 1);
+    }
+    groups = std::min(groups, (uint32_t)V.CB / kBitRows);
+    most = kBitMaxGroups;
+    parts = 1;
+    while (parts < groups && tiles * lengths * parts < kEnough) parts *= 2;
+    if (parts > 1) {
+        most = (int)std::min<uint32_t>(kBitMaxGroups, (groups + parts - 1) / parts);
+        parts = (groups + most - 1) / most;
+    }
+}
+
 static bool edges_bits_applies(const DevVocab &V)
 {
     return V.bits != 0 && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, 1) <= kMaxLdsBytes;
@@ -404,12 +432,13 @@ hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64
             X.rbn = G.rbn;
             X.splits = col_splits(G.blocks, V.CB);
             X.hi = L.hi;
-            X.most = kBitMaxGroups;
+            uint32_t parts;
+            bits_parts(V, h_maxrp, L, (uint64_t)G.blocks * X.splits, X.most, parts);
             uint32_t lds = edges_bits_lds_bytes(L.hi, bit_tab(V), bit_wmax(V), V, X.most);
             void *args[] = {&Vc, &Ec, &X, &lds};
             hipError_t e = launch_dyn(tab.edges_bits[V.bits - 2][L.range],
-                                      dim3((uint32_t)((uint64_t)G.blocks * X.splits), (uint32_t)(L.hi - L.lo + 1), 1), lds, fork,
-                                      args);
+                                      dim3((uint32_t)((uint64_t)G.blocks * X.splits), (uint32_t)(L.hi - L.lo + 1), parts),
+                                      lds, fork, args);
             if (e != hipSuccess) return e;
         }
         return fork.end();

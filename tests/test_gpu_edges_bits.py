@@ -51,3 +51,14 @@ def test_edges_of_large_blocks(scheme, A, n, lmax):
         print(f"[gpu case] edges {scheme} {n} words, pairs {a}..{b}", flush=True)
         _check(dv, v, sim, gap, 40, 100, a, b, (None, 0.3))
         _check(dv, v, sim, gap, -1000, 1000, a, min(b, a + 40000))
+
+
+@pytest.mark.parametrize("scheme,A", [("plain", 4), ("matrix", 64)])
+@pytest.mark.parametrize("n,lo,hi", [(31, 6, 6), (300, 24, 24), (2300, 24, 24), (700, 48, 48), (1500, 44, 48)])
+def test_edges_of_few_lengths(scheme, A, n, lo, hi):
+    v = synth.uniform_vocab(n, seed=n + lo, alphabet=A, min_len=lo, max_len=hi)
+    dv, sim, gap = _load(scheme, A, v)
+    pairs = n * (n - 1) // 2
+    print(f"[gpu case] edges {scheme} {n} words of {lo}..{hi}", flush=True)
+    _check(dv, v, sim, gap, 20, 100, 0, pairs, (None, 0.5))
+    _check(dv, v, sim, gap, -1000, 1000, pairs // 3 + 1, min(pairs, pairs // 3 + 150001))

@@ -101,3 +101,23 @@ def check_packed_topk(R):
 def test_packed_topk_thresholds(recorder_library):
     """The packed main pass pays more for a candidate than the plane kernels do."""
     _child(recorder_library, "check_packed_topk")
+
+
+def _edges(R, h, a, b):
+    f = R.nw._EdgeFilter(1, 60, 100, 1)
+    P = R.P
+    return R.launches(R.lib.nw_all_pairs_edges, h, a, b, ctypes.byref(f), P(1 << 41), P(1 << 42), P(1 << 43), 1 << 20,
+                      P(1 << 44), None)
+
+
+def check_few_lengths_edges(R):
+    # 2,300 words of one length: 45 tiles of eight row groups, one workgroup a tile before
+    for n, length, want in ((2300, 24, 300), (700, 48, 40)):
+        for sc in (R.nw.Scoring(40, 1, -1, -1), R.nw.Scoring(40, 0, -1, -1)):
+            h = R.load(*words(n, 40, length, length), sc)
+            grids = [g for name, g, *_ in _edges(R, h, 0, n * (n - 1) // 2) if "k_edges_bits" in name]
+            assert sum(x * y * z for x, y, z in grids) >= want, grids
+
+
+def test_edges_of_few_lengths_fill_the_chip(recorder_library):
+    _child(recorder_library, "check_few_lengths_edges")
