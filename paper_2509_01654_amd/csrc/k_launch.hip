@@ -405,9 +405,14 @@ static void bits_parts(const DevVocab &V, const uint32_t *h_maxrp, const LengthR
     }
 }
 
+// A few words make one workgroup, whose 32-row steps take longer than the packed
+// rows.  Packed / planes, us: one length of 48 symbols, 6 words 91 / 106, 8 words
+// 104 / 106 (two planes); 12 words 143 / 190, 16 words 173 / 191, lengths 1..48, 24
+// words 174 / 213, 32 words 207 / 217 (three).
+static int64_t edges_bits_min_words(const DevVocab &V) { return V.bits == 2 ? 8 : 32; }
 static bool edges_bits_applies(const DevVocab &V)
 {
-    return V.bits != 0 && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, 1) <= kMaxLdsBytes;
+    return V.bits != 0 && V.n >= edges_bits_min_words(V) && !packed_dp_only() && edges_bits_lds_bytes(V.lmax, bit_tab(V), bit_wmax(V), V, 1) <= kMaxLdsBytes;
 }
 
 hipError_t launch_edges_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,

@@ -121,3 +121,15 @@ def check_few_lengths_edges(R):
 
 def test_edges_of_few_lengths_fill_the_chip(recorder_library):
     _child(recorder_library, "check_few_lengths_edges")
+
+
+def check_tiny_edges(R):
+    for sc, least in ((R.nw.Scoring(40, 1, -1, -1), 8), (R.nw.Scoring(40, 0, -1, -1), 32)):
+        for n, planes in ((2, False), (least - 1, False), (least, True)):
+            h = R.load(*words(n, 40, 48, 48), sc)
+            names = [x[0] for x in _edges(R, h, 0, n * (n - 1) // 2)]
+            assert any("k_edges_bits" in x for x in names) == planes, (n, names)
+
+
+def test_edges_of_a_few_words_stay_packed(recorder_library):
+    _child(recorder_library, "check_tiny_edges")
