@@ -182,26 +182,17 @@ static bool packed_dp_only()
 static int bit_tab(const DevVocab &V) { return V.bits == 2 ? Bits2::kTab : Bits3::kTab; }
 static int bit_wmax(const DevVocab &V) { return V.bits == 2 ? Bits2::kWmax : Bits3::kWmax; }
 
-// Scores (not edges) of dictionaries the bit planes hold, where the staging
-// and one group of the longest row words fit in LDS.  16-bit staging covers
-// every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
-// Three planes at up to 2,304 words past 12 symbols stay with the packed
-// kernels: a block has few groups of 32 rows there, whose tables serve few
-// columns, and what counts is the length of one workgroup.  Packed / planes,
-// int16, us: 79 / 86 at 500 words to 18 symbols, 85 / 107 to 30, 108 / 142 to
-// 42; 77 / 85, 116 / 125 and 158 / 163 at 2,000 words, 109 / 91, 204 / 138 and
-// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.  Eight dictionaries
-// in one batch, the largest of 2,200 / 2,500 words to 48 symbols: 372 / 388
-// and 427 / 412.
-constexpr int64_t kPlanesAboveWords = 2304;
-constexpr int kPlanesShortWords = 12;
-bool triangle_bits_applies(const DevVocab &V, int out_kind)
+// Launches of the packed triangle kernels of dictionaries up to
+// kClassLaunchMaxWords words: one per class of 8 row lengths present.
+static uint32_t class_launches(const DevVocab &V, const uint32_t *h_maxrp)
 {
-    if (V.bits == 0 || out_kind == OUT_EDGES || packed_dp_only()) return false;
-    const bool w16 = tri_bits_wide(V);
-    if (w16 && V.bits == 2) return false;
-    if (V.bits == 3 && V.lmax > kPlanesShortWords && V.n <= kPlanesAboveWords) return false;
-    return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16) <= kMaxLdsBytes;
+    uint32_t launches = 0;
+    for (int lo = 0; lo <= V.lmax; lo += 8) {
+        uint32_t rows = 0;
+        for (int LA = lo; LA <= std::min(lo + 7, (int)V.lmax); ++LA) rows += h_maxrp[LA];
+        launches += rows > 0;
+    }
+    return launches;
 }
 
 // The launches of a bit-plane triangle or edge call over the lengths present in h_maxrp:
@@ -222,31 +213,67 @@ static std::vector<LengthRange> bits_launches(const DevVocab &V, const uint32_t 
     return out;
 }
 
+// Scores (not edges) of dictionaries the bit planes hold, where the staging
+// and one group of the longest row words fit in LDS.  16-bit staging covers
+// every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
+// Three planes at up to 2,304 words past 12 symbols stay with the packed
+// kernels: a block has few groups of 32 rows there, whose tables serve few
+// columns, and what counts is the length of one workgroup.  Packed / planes,
+// int16, us: 79 / 86 at 500 words to 18 symbols, 85 / 107 to 30, 108 / 142 to
+// 42; 77 / 85, 116 / 125 and 158 / 163 at 2,000 words, 109 / 91, 204 / 138 and
+// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.  Eight dictionaries
+// in one batch, the largest of 2,200 / 2,500 words to 48 symbols: 372 / 388
+// and 427 / 412.
+constexpr int64_t kPlanesAboveWords = 2304;
+constexpr int kPlanesShortWords = 12;
+static bool triangle_bits_applies(const DevVocab &V, int out_kind)
+{
+    if (V.bits == 0 || out_kind == OUT_EDGES || packed_dp_only()) return false;
+    const bool w16 = tri_bits_wide(V);
+    if (w16 && V.bits == 2) return false;
+    if (V.bits == 3 && V.lmax > kPlanesShortWords && V.n <= kPlanesAboveWords) return false;
+    return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16, 1) <= kMaxLdsBytes;
+}
+
 static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
                                        int out_kind, void *d_out, StreamFork &fork)
 {
     const KernelTables &tab = kernel_tables();
     const bool w16 = tri_bits_wide(V);
     const int scheme = w16 ? 4 : 2 * (V.bits - 2) + (out_kind == OUT_I8 ? 0 : 1);
-    uint32_t rb0 = (uint32_t)(row_of_index(V.n, idx_begin) / V.CB);
-    const uint32_t nr = (uint32_t)(row_of_index(V.n, idx_end - 1) / V.CB) - rb0 + 1;
+    const int64_t row0 = row_of_index(V.n, idx_begin), row1 = row_of_index(V.n, idx_end - 1);
+    uint32_t rb0 = (uint32_t)(row0 / V.CB);
+    const uint32_t nr = (uint32_t)(row1 / V.CB) - rb0 + 1;
+    const std::vector<LengthRange> launches = bits_launches(V, h_maxrp);
+    // Groups a workgroup takes at a time: one table build serves them, but they
+    // run one after the other, so fewer where the call has less than kEnough
+    // workgroups.  Four / one, words of one length, int16, us: 2,300 words of 24
+    // symbols 90 / 48, 4,000 words of 24 symbols under a matrix 295 / 191.
+    int most = kTriBitGroups;
+    {
+        constexpr uint64_t kEnough = 1024;
+        const uint64_t tiles = std::max<uint64_t>(1, (uint64_t)nr * V.nwin / 2);
+        const uint64_t groups = ((uint64_t)std::min<int64_t>(row1 - row0 + 1, V.CB) + kBitRows - 1) / kBitRows;
+        uint64_t lengths = 0;
+        for (int LA = 0; LA <= V.lmax; ++LA) lengths += h_maxrp[LA] != 0;
+        while (most > 1 && tiles * std::max(std::min(lengths, groups), groups / most) < kEnough) most /= 2;
+    }
     // A workgroup takes one chunk of row groups (blockIdx.z) against nw
     // windows, its tables serving all of them: as many as leave kWorkgroups
     // workgroups.
     auto parts = [&](const LengthRange &L) {
-        const uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16);
-        uint32_t most = 1;
+        const uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16, most);
+        uint32_t parts = 1;
         for (int LA = L.lo; LA <= L.hi; ++LA) {
             // rows of longest length LA: those of that length, and up to a
             // group's worth of shorter ones at either end
             const uint32_t groups = h_maxrp[LA] * 2 / kBitRows + 2;
-            const uint32_t kg = (uint32_t)tri_bits_groups(LA, bit_tab(V), V.alphabet, V.TW, V.CB, w16, lds);
-            if (h_maxrp[LA]) most = std::max(most, (groups + kg - 1) / kg);
+            const uint32_t kg = (uint32_t)tri_bits_groups(LA, bit_tab(V), V.alphabet, V.TW, V.CB, w16, lds, most);
+            if (h_maxrp[LA]) parts = std::max(parts, (groups + kg - 1) / kg);
         }
-        return most;
+        return parts;
     };
     constexpr uint64_t kWorkgroups = 8192;
-    const std::vector<LengthRange> launches = bits_launches(V, h_maxrp);
     uint64_t chunks = 0;
     for (const LengthRange &L : launches) chunks += (uint64_t)parts(L) * (uint64_t)(L.hi - L.lo + 1);
     int nw = (int)std::max<uint64_t>(1, std::min<uint64_t>(8, chunks * nr * V.nwin / 2 / kWorkgroups));
@@ -255,9 +282,9 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
         DevVocab Vc = V;
         uint64_t ib = idx_begin, ie = idx_end;
         void *po = d_out;
-        uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16);
+        uint32_t lds = tri_bits_lds_bytes(L.hi, bit_tab(V), V, w16, most);
         int hi = L.hi;
-        void *args[] = {&Vc, &ib, &ie, &po, &rb0, &nset, &nw, &hi, &lds};
+        void *args[] = {&Vc, &ib, &ie, &po, &rb0, &nset, &nw, &hi, &lds, &most};
         hipError_t e = launch_dyn(tab.tri_bits[scheme][L.range],
                                   dim3(nr * nset, (uint32_t)(L.hi - L.lo + 1), parts(L)), lds, fork, args,
                                   tab.tri_bits_threads[scheme][L.range]);
@@ -269,14 +296,11 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
 uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind)
 {
     if (V.n < 2) return 0;
-    if (triangle_bits_applies(V, out_kind)) return (uint32_t)bits_launches(V, h_maxrp).size();
-    const int per = V.n <= kClassLaunchMaxWords ? 8 : 1;
+    if (triangle_bits_applies(V, out_kind))
+        return (uint32_t)bits_launches(V, h_maxrp).size();
+    if (V.n <= kClassLaunchMaxWords) return class_launches(V, h_maxrp);
     uint32_t launches = 0;
-    for (int lo = 0; lo <= V.lmax; lo += per) {
-        uint32_t rows = 0;
-        for (int LA = lo; LA <= std::min(lo + per - 1, (int)V.lmax); ++LA) rows += h_maxrp[LA];
-        launches += rows > 0;
-    }
+    for (int LA = 0; LA <= V.lmax; ++LA) launches += h_maxrp[LA] > 0;
     return launches;
 }
 

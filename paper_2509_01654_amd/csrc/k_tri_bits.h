@@ -32,7 +32,7 @@
 
 namespace nw {
 
-constexpr int kTriBitGroups = 4;    // groups whose tables are built at a time
+constexpr int kTriBitGroups = 4;    // groups whose tables are built at a time, at most
 constexpr uint32_t kTriBitsLds = 40u * 1024u;   // aim: four workgroups per CU
 
 struct alignas(16) TriRow {
@@ -52,18 +52,19 @@ __host__ __device__ constexpr uint32_t tri_bits_fixed_bytes(int TW, int CB, bool
     const uint32_t stage = tri_stage_stride(TW) * (w16 ? 16u : 8u), list = (uint32_t)CB * 2u;
     return ((stage > list ? stage : list) + 15u & ~15u) + 64u;
 }
-__host__ __device__ inline int tri_bits_groups(int LA, int tab, int alphabet, int TW, int CB, bool w16, uint32_t lds)
+__host__ __device__ inline int tri_bits_groups(int LA, int tab, int alphabet, int TW, int CB, bool w16, uint32_t lds, int most)
 {
     const uint32_t per = tri_bits_group_bytes(LA, tab, alphabet), fixed = tri_bits_fixed_bytes(TW, CB, w16);
     if (lds < fixed + per) return 0;
     const uint32_t kg = (lds - fixed) / per;
-    return kg < (uint32_t)kTriBitGroups ? (int)kg : kTriBitGroups;
+    return kg < (uint32_t)most ? (int)kg : most;
 }
-// LDS of a launch whose longest row words have LA symbols.
-__host__ __device__ inline uint32_t tri_bits_lds_bytes(int LA, int tab, const DevVocab &V, bool w16)
+// LDS of a launch whose longest row words have LA symbols, for at most `most`
+// (1 .. kTriBitGroups) groups at a time.
+__host__ __device__ inline uint32_t tri_bits_lds_bytes(int LA, int tab, const DevVocab &V, bool w16, int most)
 {
     const uint32_t fixed = tri_bits_fixed_bytes(V.TW, V.CB, w16), per = tri_bits_group_bytes(LA, tab, V.alphabet);
-    return bit_lds_bytes(fixed, per, kTriBitsLds, (uint32_t)kTriBitGroups);
+    return bit_lds_bytes(fixed, per, kTriBitsLds, (uint32_t)most);
 }
 // More than 256 score values: 16-bit staging.
 __host__ __device__ inline bool tri_bits_wide(const DevVocab &V) { return V.hi - V.lo > 255; }
@@ -124,7 +125,7 @@ __device__ __forceinline__ void store_eight(const TriRow &R, int f, const uint32
 
 template <int LA, class S, int ES, bool W16, int NT>
 __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uint32_t w0, int nw, uint32_t part, uint64_t idx_begin,
-                                              uint64_t idx_end, void *out, uint32_t lds_bytes, uint8_t *lds)
+                                              uint64_t idx_end, void *out, uint32_t lds_bytes, int most, uint8_t *lds)
 {
     constexpr int P = sum_planes<LA, S>();
     constexpr int PD = P > 0 ? P : 1;
@@ -176,7 +177,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
     uint32_t *counts = reinterpret_cast<uint32_t *>(lds + tri_bits_fixed_bytes(TW, V.CB, W16) - 64u);
     uint8_t *groups = lds + tri_bits_fixed_bytes(TW, V.CB, W16);
     const uint32_t gstride = tri_bits_group_bytes(LA, S::kTab, A);
-    const int kg = tri_bits_groups(LA, S::kTab, A, TW, V.CB, W16, lds_bytes);
+    const int kg = tri_bits_groups(LA, S::kTab, A, TW, V.CB, W16, lds_bytes, most);
     if (kg < 1) return;   // the launch's LDS holds a group (tri_bits_lds_bytes)
 
     // the groups of this length: the block's own, or groups of the listed rows
@@ -387,14 +388,15 @@ constexpr int tri_bits_threads() { return W16 && HI > 12 ? 512 : 256; }
 template <int LO, int HI, class S, int ES, bool W16>
 __global__ __launch_bounds__((tri_bits_threads<HI, W16>())) __attribute__((amdgpu_waves_per_eu(bits_min_waves<HI, S>())))
 void k_tri_bits(DevVocab V, uint64_t idx_begin, uint64_t idx_end, void *out, uint32_t rb0, uint32_t nset, int nw,
-                int hi, uint32_t lds_bytes)
+                int hi, uint32_t lds_bytes, int most)
 {
     extern __shared__ __align__(16) uint8_t lds[];
     const uint32_t r = rb0 + blockIdx.x / nset, w0 = blockIdx.x % nset * (uint32_t)nw;
     const int LA = hi - (int)blockIdx.y;
     if (LA < LO || LA > HI) return;
     bit_length_dispatch<LO, HI>(LA, [&](auto la) {
-        tri_bits_tile<decltype(la)::value, S, ES, W16, tri_bits_threads<HI, W16>()>(V, r, w0, nw, blockIdx.z, idx_begin, idx_end, out, lds_bytes, lds);
+        tri_bits_tile<decltype(la)::value, S, ES, W16, tri_bits_threads<HI, W16>()>(V, r, w0, nw, blockIdx.z, idx_begin, idx_end, out, lds_bytes,
+                                                                                  most, lds);
     });
 }
 

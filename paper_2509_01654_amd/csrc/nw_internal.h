@@ -155,9 +155,6 @@ class StreamFork;
 hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
                                  int out_kind, void *d_out, hipStream_t stream, const EdgeSink *E = nullptr,
                                  StreamFork *shared = nullptr);
-// The same for dictionaries the bit-plane kernels hold (triangle_bits_applies),
-// int8 / int16 scores only; h_maxrp tells the lengths present.
-bool triangle_bits_applies(const DevVocab &V, int out_kind);
 // Launches launch_triangle_tiled issues for a whole triangle.
 uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind);
 hipError_t launch_triangle_naive(const DevVocab &V, uint64_t idx_begin, uint64_t idx_end, int out_kind,

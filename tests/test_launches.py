@@ -133,3 +133,27 @@ def check_tiny_edges(R):
 
 def test_edges_of_a_few_words_stay_packed(recorder_library):
     _child(recorder_library, "check_tiny_edges")
+
+
+def _triangle(R, h, a, b, dtype=2):
+    return R.launches(R.lib.nw_all_pairs_scores, h, a, b, dtype, R.P(1 << 41), None)
+
+
+def _planes(launches):
+    kinds = {"k_tri_bits" in x[0] for x in launches}
+    assert len(kinds) == 1, launches
+    return kinds.pop()
+
+
+PLAIN, MATRIX = (1, -1, -1), (0, -1, -1)   # two planes; three
+
+
+def check_few_lengths_triangle(R):
+    for sc, n, length in ((PLAIN, 2300, 24), (MATRIX, 4000, 24)):
+        h = R.load(*words(n, 40, length, length), R.nw.Scoring(40, *sc))
+        out = _triangle(R, h, 0, n * (n - 1) // 2)
+        assert _planes(out) and sum(x * y * z for _, (x, y, z), *_ in out) >= 500, out
+
+
+def test_triangle_of_few_lengths_fills_the_chip(recorder_library):
+    _child(recorder_library, "check_few_lengths_triangle")
