@@ -213,26 +213,61 @@ static std::vector<LengthRange> bits_launches(const DevVocab &V, const uint32_t 
     return out;
 }
 
+// Whether planes are the faster for the scores of pair indices [idx_begin, idx_end)
+// of a dictionary of up to kClassLaunchMaxWords words.  They score 32 rows at once,
+// so the least time of a workgroup is 7 (two planes) or 22 (three) instructions for
+// every cell of the longest words, against 1 for a packed pair of rows; they save
+// launches (one per 24 or 12 row lengths against one per 8) and the rows of a block
+// outside the range.  The lines are from 2,500 random calls timed on both sides
+// (2 .. 16,384 words, 4 to 200 symbols, mixed, narrow and single lengths to 48, whole
+// triangles and ranges); the choice costs 1.2 % (two planes) and 1.6 % (three) over
+// the better side on average, planes wherever they apply 6 % and 18 %.
+// - Two planes, and three up to 12 symbols: but for short calls that are one launch
+//   on either side.  Words of one length, int16, packed / planes, us: two planes, 200
+//   words of 24 / 48 symbols 30 / 40, 48 / 73, 700 words 34 / 40, 66 / 74, 1,500
+//   words of 24 symbols 58 / 40; three, 700 / 1,500 / 2,300 words of 12 symbols 28 /
+//   43, 48 / 49, 79 / 54.
+// - Three planes past 12 symbols: packed up to 2,304 words (with 16-bit staging in
+//   windows of a block, words to 48 symbols 197 / 277), then by estimates, us,
+//   fitted to the calls above (log error 0.23 packed, 0.21 planes).  A million pairs
+//   of 5,000 words of 30..48 symbols 131 / 234, of 16,384 words 475 / 257; 3,000 words
+//   to 24 symbols 149 / 97.
+static bool planes_faster(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end)
+{
+    constexpr int kPlanesShortWords = 12;
+    constexpr int64_t kOneLaunchWords = 4096, kPlanesAboveWords = 2304;
+    const uint64_t pairs = idx_end - idx_begin;
+    const uint32_t np = class_launches(V, h_maxrp), nb = (uint32_t)bits_launches(V, h_maxrp).size();
+    if (V.bits == 2 || V.lmax <= kPlanesShortWords)
+        return np > nb || V.n > kOneLaunchWords || pairs >= (V.bits == 2 ? 330000u : 900000u);
+    if (V.n <= kPlanesAboveWords) return false;
+    double block_pairs = 0, rows = 0, symbols = 0;   // pairs of the block rows the range touches
+    const int64_t r0 = row_of_index(V.n, idx_begin) / V.CB, r1 = row_of_index(V.n, idx_end - 1) / V.CB;
+    for (int64_t r = r0; r <= r1; ++r)
+        block_pairs += (double)(std::min<int64_t>(V.n, (r + 1) * V.CB) - r * V.CB) * (double)(V.n - r * V.CB);
+    for (int LA = 0; LA <= V.lmax; ++LA) {
+        rows += h_maxrp[LA];
+        symbols += (double)LA * h_maxrp[LA];
+    }
+    const double cells = symbols / rows * (symbols / rows) * 1e-9;   // of a pair of mean lengths, in 1e9
+    const int steps = std::max(1, V.TW / (tri_bits_wide(V) ? 512 : 256));   // 64-column steps of a wavefront
+    const double packed = 40 + 8.4 * np + 65 * block_pairs * cells;
+    const double planes = 45 + 0.75 * V.lmax + 0.025 * steps * V.lmax * V.lmax + 26 * (double)pairs * cells;
+    return planes < packed;
+}
+
 // Scores (not edges) of dictionaries the bit planes hold, where the staging
 // and one group of the longest row words fit in LDS.  16-bit staging covers
 // every score range of Bits3; Bits2 ranges fit a byte (at most 5 x 48 values).
-// Three planes at up to 2,304 words past 12 symbols stay with the packed
-// kernels: a block has few groups of 32 rows there, whose tables serve few
-// columns, and what counts is the length of one workgroup.  Packed / planes,
-// int16, us: 79 / 86 at 500 words to 18 symbols, 85 / 107 to 30, 108 / 142 to
-// 42; 77 / 85, 116 / 125 and 158 / 163 at 2,000 words, 109 / 91, 204 / 138 and
-// 272 / 222 at 3,000; to 12 symbols 61 / 52 at 500 words.  Eight dictionaries
-// in one batch, the largest of 2,200 / 2,500 words to 48 symbols: 372 / 388
-// and 427 / 412.
-constexpr int64_t kPlanesAboveWords = 2304;
-constexpr int kPlanesShortWords = 12;
-static bool triangle_bits_applies(const DevVocab &V, int out_kind)
+// Above kClassLaunchMaxWords words planes are the faster in every form measured.
+static bool triangle_bits_applies(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
+                                  int out_kind)
 {
     if (V.bits == 0 || out_kind == OUT_EDGES || packed_dp_only()) return false;
     const bool w16 = tri_bits_wide(V);
     if (w16 && V.bits == 2) return false;
-    if (V.bits == 3 && V.lmax > kPlanesShortWords && V.n <= kPlanesAboveWords) return false;
-    return tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16, 1) <= kMaxLdsBytes;
+    if (tri_bits_lds_bytes(V.lmax, bit_tab(V), V, w16, 1) > kMaxLdsBytes) return false;
+    return V.n > kClassLaunchMaxWords || planes_faster(V, h_maxrp, idx_begin, idx_end);
 }
 
 static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxrp, uint64_t idx_begin, uint64_t idx_end,
@@ -296,7 +331,7 @@ static hipError_t launch_triangle_bits(const DevVocab &V, const uint32_t *h_maxr
 uint32_t triangle_launches(const DevVocab &V, const uint32_t *h_maxrp, int out_kind)
 {
     if (V.n < 2) return 0;
-    if (triangle_bits_applies(V, out_kind))
+    if (triangle_bits_applies(V, h_maxrp, 0, (uint64_t)V.n * (uint64_t)(V.n - 1) / 2, out_kind))
         return (uint32_t)bits_launches(V, h_maxrp).size();
     if (V.n <= kClassLaunchMaxWords) return class_launches(V, h_maxrp);
     uint32_t launches = 0;
@@ -316,7 +351,7 @@ hipError_t launch_triangle_tiled(const DevVocab &V, const uint32_t *h_maxrp, uin
         if (ef != hipSuccess) return ef;
     }
     StreamFork &fork = shared ? *shared : own;
-    if (triangle_bits_applies(V, out_kind)) {
+    if (triangle_bits_applies(V, h_maxrp, idx_begin, idx_end, out_kind)) {
         const hipError_t e = launch_triangle_bits(V, h_maxrp, idx_begin, idx_end, out_kind, d_out, fork);
         if (e != hipSuccess) return e;
         return shared ? hipSuccess : own.end();

@@ -148,6 +148,29 @@ def _planes(launches):
 PLAIN, MATRIX = (1, -1, -1), (0, -1, -1)   # two planes; three
 
 
+def check_triangle_routes(R):
+    # scoring, words, lengths, share of the triangle, planes or not: calls where one
+    # side was measured well ahead
+    for sc, n, lo, hi, share, planes in [
+            (PLAIN, 2, 12, 12, 1, False), (PLAIN, 4, 48, 48, 1, False), (PLAIN, 300, 1, 16, 1, True),
+            (PLAIN, 200, 24, 24, 1, False), (PLAIN, 700, 48, 48, 1, False), (PLAIN, 1500, 24, 24, 1, True),
+            (PLAIN, 2000, 1, 20, 1, True), (PLAIN, 300, 22, 26, 1, False), (PLAIN, 1500, 44, 48, 1, True),
+            (PLAIN, 5000, 1, 48, 1e-4, True), (MATRIX, 700, 12, 12, 1, False), (MATRIX, 3100, 12, 12, 1, True),
+            (MATRIX, 300, 1, 12, 1, True), (MATRIX, 2304, 1, 16, 1, False), (MATRIX, 6000, 1, 13, 1, True),
+            (MATRIX, 5000, 30, 48, 0.01, False), (MATRIX, 16000, 30, 48, 1e-5, True), (MATRIX, 12000, 30, 48, 0.1, True),
+            (MATRIX, 17000, 1, 48, 1e-4, True)]:
+        h = R.load(*words(n, 40, lo, hi), R.nw.Scoring(40, *sc))
+        pairs = n * (n - 1) // 2
+        a = pairs // 3 if share < 1 else 0
+        got = _planes(_triangle(R, h, a, min(pairs, a + max(1, int(pairs * share)))))
+        assert got == planes, (sc, n, lo, hi, share, got)
+
+
+def test_small_triangles_stay_packed(recorder_library):
+    """Dictionaries of a few words or few lengths, and ranges of few pairs under three planes."""
+    _child(recorder_library, "check_triangle_routes")
+
+
 def check_few_lengths_triangle(R):
     for sc, n, length in ((PLAIN, 2300, 24), (MATRIX, 4000, 24)):
         h = R.load(*words(n, 40, length, length), R.nw.Scoring(40, *sc))
