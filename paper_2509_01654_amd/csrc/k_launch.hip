@@ -704,10 +704,10 @@ hipError_t launch_merge(const uint64_t *partial, int P, int kin, int64_t rows, i
 }
 
 __global__ __launch_bounds__(256) void k_column_layout(const uint8_t *csym, const uint8_t *len, const uint16_t *col,
-                                                       int window, int WB, int64_t ndw, uint32_t *ccol)
+                                                       int window, int WB, int64_t begin, int64_t end, uint32_t *ccol)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= ndw) return;
+    const int64_t t = begin + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= end) return;
     const int lane = (int)(t & 63);
     const int64_t gq = t >> 6, g = gq / kColDwords;
     const int q = (int)(gq % kColDwords);
@@ -726,11 +726,17 @@ __global__ __launch_bounds__(256) void k_column_layout(const uint8_t *csym, cons
 hipError_t launch_column_layout(const DevVocab &V, const uint8_t *len, const uint16_t *col, int window, int64_t nslots,
                                 uint32_t *ccol, hipStream_t stream)
 {
+    // a thread per dword, in launches of 2^30 threads (a grid holds fewer than 2^32)
+    constexpr int64_t kSlice = (int64_t)1 << 30;
     const int64_t ndw = nslots * kColDwords;
-    if (ndw == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((ndw + 255) / 256)), dim3(256), 0, stream, V.csym, len, col,
-                       window, V.WB, ndw, ccol);
-    return hipGetLastError();
+    for (int64_t b = 0; b < ndw; b += kSlice) {
+        const int64_t e = std::min(ndw, b + kSlice);
+        hipLaunchKernelGGL(k_column_layout, dim3((uint32_t)((e - b + 255) / 256)), dim3(256), 0, stream, V.csym, len, col,
+                           window, V.WB, b, e, ccol);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
 }
 
 // The main pass takes the bit-plane kernels where the scoring fits them and

@@ -16,6 +16,7 @@ struct record { char name[512]; uint32_t grid[3], block[3]; uint64_t lds; uint64
 static struct record recs[4096];
 static int nrecs;
 static uintptr_t next_handle = 0x1000;
+static int last_error;
 
 int rec_count(void) { return nrecs; }
 void rec_clear(void) { nrecs = 0; }
@@ -35,7 +36,7 @@ int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t lds, pt
         r->stream = (uint64_t)(uintptr_t)stream;
     }
     /* the runtime's own limit: fewer than 2^32 threads in a dimension of the grid */
-    if ((uint64_t)g.x * b.x >> 32 || (uint64_t)g.y * b.y >> 32 || (uint64_t)g.z * b.z >> 32) return 9;
+    if ((uint64_t)g.x * b.x >> 32 || (uint64_t)g.y * b.y >> 32 || (uint64_t)g.z * b.z >> 32) return last_error = 9;
     return 0;
 }
 
@@ -63,7 +64,12 @@ int hipEventSynchronize(ptr e) { (void)e; return 0; }
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int d) { (void)d; return 0; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void)
+{
+    const int e = last_error;
+    last_error = 0;
+    return e;
+}
 int hipGetSymbolAddress(ptr *p, const void *s) { (void)s; *p = (ptr)((uintptr_t)1 << 44); return 0; }
 int hipHostMalloc(ptr *p, size_t n, unsigned f) { (void)n; (void)f; *p = NULL; return 2; }
 int hipLaunchHostFunc(ptr s, void (*fn)(void *), void *arg) { (void)s; fn(arg); return 0; }

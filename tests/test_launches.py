@@ -180,3 +180,21 @@ def check_few_lengths_triangle(R):
 
 def test_triangle_of_few_lengths_fills_the_chip(recorder_library):
     _child(recorder_library, "check_few_lengths_triangle")
+
+
+def check_column_layout(R):
+    # nw::launch_column_layout(vocab, lengths, columns, window, slots, out, stream)
+    fn = R.lib._ZN2nw20launch_column_layoutERKNS_8DevVocabEPKhPKtilPjP12ihipStream_t
+    fn.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
+    fn.restype = ctypes.c_int
+    vocab = ctypes.create_string_buffer(4096)
+    for slots in (256, 3072 * 1000, 400_000_128, 2_147_480_576):
+        R.hip.rec_clear()
+        assert fn(vocab, None, None, 1024, slots, R.P(1 << 41), None) == 0, slots
+        threads = sum(r.grid[0] * r.block[0] for r in (R.hip.rec_get(i).contents for i in range(R.hip.rec_count())))
+        assert 12 * slots <= threads < 12 * slots + 256 * R.hip.rec_count(), (slots, threads)
+
+
+def test_column_layout_of_the_largest_dictionaries(recorder_library):
+    """A grid holds fewer than 2^32 threads: the layout of 357 million words and more goes in several launches."""
+    _child(recorder_library, "check_column_layout")
