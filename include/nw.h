@@ -296,10 +296,11 @@ int nw_query_workspace_bytes(const nw_vocab *v, uint64_t n_q, uint64_t q_symbols
  * its k best dictionary neighbours over all dictionary words d (no
  * self-exclusion), A = the query word: d_score[q*k + r], d_index[q*k + r].
  * The similar-word lookup the paper envisions (Section 6).  Enqueued on
- * hip_stream; the host arrays may be reused when the call returns (the
- * library's host image of the batch is released by a host callback on the
- * stream once its copy is done, which is why the call refuses a capturing
- * stream).
+ * hip_stream, and on no other stream; the host arrays may be reused when the
+ * call returns (a batch whose packed image is up to 24 KiB, about 370 queries,
+ * goes up as kernel arguments; a larger image is copied, and released by a host
+ * callback on the stream once its copy is done, which is why the call refuses a
+ * capturing stream).
  * Errors: NW_EINVAL (k outside 1..64, bad query words, a capturing stream),
  * NW_ERANGE (query scores could leave int16), NW_ENOMEM (workspace too
  * small). */

@@ -40,6 +40,9 @@ def _units():
     for variant, rng in _ranges("NW_TRI_BITS"):
         units.append((f"k_tri_bits_inst_{variant}_{rng}", os.path.join(CSRC, "k_tri_bits_inst.hip"),
                       [f"-DNW_VARIANT={variant}", f"-DNW_RANGE={rng}"]))
+    for lo, hi in reversed(_ranges("NW_QUERY")):
+        units.append((f"k_query_inst_{lo}_{hi}", os.path.join(CSRC, "k_query_inst.hip"),
+                      [f"-DNW_QUERY_LO={lo}", f"-DNW_QUERY_HI={hi}"]))
     units.append(("k_probe_bits_inst", os.path.join(CSRC, "k_probe_bits_inst.hip"), []))
     units += [
         ("nw_api", os.path.join(CSRC, "nw_api.cpp"), []),

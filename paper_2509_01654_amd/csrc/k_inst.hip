@@ -1,4 +1,4 @@
-// k_inst.hip -- instantiates the tiled kernels (triangle, query, top-k) for
+// k_inst.hip -- instantiates the tiled kernels (triangle, edges, top-k) for
 // row lengths LA in [NW_LA_LO, NW_LA_HI]; compiled once per range so the
 // instances build in parallel.  Exports their addresses through
 // nw_fill_<NW_LA_LO>.
@@ -7,7 +7,6 @@
 #include "k_batch.h"
 #include "k_edges.h"
 #include "k_probe.h"
-#include "k_query.h"
 #include "k_topk.h"
 #include "k_topk_code.h"
 #include "k_tri_code.h"
@@ -34,7 +33,6 @@ static void fill(KernelTables &t, std::integer_sequence<int, Is...>)
     ((t.tri[LO + Is] = reinterpret_cast<const void *>(&k_tri_tiled<LO + Is>)), ...);
     ((t.tri_code1[LO + Is] = reinterpret_cast<const void *>(&k_tri_code<LO + Is, 1>)), ...);
     ((t.tri_code2[LO + Is] = tri_code2_kernel<LO + Is>()), ...);
-    ((t.query[LO + Is] = reinterpret_cast<const void *>(&k_query_tiled<LO + Is>)), ...);
     ((t.probe_thr[LO + Is] = reinterpret_cast<const void *>(&k_probe_thr<LO + Is>)), ...);
     ((t.topk[LO + Is] = reinterpret_cast<const void *>(&k_topk_tiled<LO + Is>)), ...);
     ((t.topk_code[LO + Is] = reinterpret_cast<const void *>(&k_topk_code<LO + Is, topk_code_pairs(LO + Is)>)), ...);

@@ -95,6 +95,9 @@ const KernelTables &kernel_tables()
 #define X(lo, hi) nw_fill_class_##lo(t);
         NW_CLASS8
 #undef X
+#define X(lo, hi) nw_fill_query_##lo(t);
+        NW_QUERY
+#undef X
         return true;
     }();
     (void)init;
@@ -609,12 +612,12 @@ hipError_t launch_query(const DevVocab &V, const RowSet &R, const uint32_t *h_of
     }
     int64_t per = (C.nslots + nsplit - 1) / nsplit;
     per = (per + kThreads - 1) / kThreads * kThreads;
-    // a row pair per workgroup: a batch of 256 queries against 200k words took
-    // 3.9 ms with four, one after the other, 1.36 ms with one
-    const int rpw = 1;
-    for (int LA = 0; LA <= kMaxLen; ++LA) {
-        const uint32_t np = h_off[LA + 1] - h_off[LA];
+    for (int c = 0; c < kNumQuery; ++c) {
+        const int lo = kQuerySpan * c;
+        int hi = c + 1 < kNumQuery ? lo + kQuerySpan - 1 : kMaxLen;
+        const uint32_t np = h_off[hi + 1] - h_off[lo];
         if (np == 0) continue;
+        while (h_off[hi + 1] == h_off[hi]) --hi;   // the longest present: its profile is the largest
         QueryArgs Q;
         Q.R = R;
         Q.C = C;
@@ -623,19 +626,17 @@ hipError_t launch_query(const DevVocab &V, const RowSet &R, const uint32_t *h_of
         Q.gap = V.gap;
         Q.lo = V.lo;
         Q.k = k;
-        Q.rpw = rpw;
         Q.per = per;
         Q.nsplit = nsplit;
         Q.partial = partial;
         void *args[] = {&Q};
-        const dim3 grid((np + rpw - 1) / rpw, nsplit);
-        hipError_t e = launch_dyn(tab.query[LA], grid, query_lds_bytes(LA, V.alphabet, k), fork, args);
+        hipError_t e = launch_dyn(tab.query[c], dim3(np, nsplit), query_lds_bytes(hi, V.alphabet, k), fork, args);
         if (e != hipSuccess) return e;
     }
     return fork_streams ? fork.end() : hipSuccess;
 }
 
-// NW_PREPASS=lists keeps the list pre-pass (k_query_tiled + merge) where the
+// NW_PREPASS=lists keeps the list pre-pass (k_query_class + merge) where the
 // selection would apply (both give the same keys; for comparisons).
 static bool list_prepass_only()
 {

@@ -6,16 +6,24 @@
 // {(score(q, d), d)} sorted by (score descending, index ascending); there is
 // no self-exclusion here (the all-pairs path accounts for it).
 //
-// k_query_tiled<LA>: a workgroup takes `rpw` row pairs of length LA (the two
-// words of a pair fill the two binary16 halves of the DP) and one split of the
-// column slots.  Per row pair it builds the LDS profile, then each wavefront
-// walks its share of the split (64 length-sorted column words per step) and
-// keeps a sorted wave list of the best k keys for each of the two rows.  With
-// several splits the four wave lists of a row are merged in LDS (wavefront 0
-// for the first row, 1 for the second) into the split's list, written to
-// `partial`, row-major [row][split][k]; with one split (many rows, nothing to
-// spread) the four wave lists go out as they are, [row][wave][k].  Either
-// way a row has query_lists(nsplit) lists of k keys.
+// k_query_class<LO, HI>: a workgroup takes one row pair of a length in LO .. HI
+// (the two words of a pair have one length and fill the two binary16 halves of
+// the DP) and one split of the column slots.  It builds the pair's LDS profile,
+// then each wavefront walks its share of the split (64 length-sorted column
+// words per step) and keeps a sorted wave list of the best k keys for each of
+// the two rows.  With several splits the four wave lists of a row are merged in
+// LDS (wavefront 0 for the first row, 1 for the second) into the split's list,
+// written to `partial`, row-major [row][split][k]; with one split (many rows,
+// nothing to spread) the four wave lists go out as they are, [row][wave][k].
+// Either way a row has query_lists(nsplit) lists of k keys.
+//
+// A launch per range of 16 lengths, not per length: a batch of mixed lengths is
+// at most three launches on the caller's stream, its row pairs side by side, with
+// no need of other streams.  8 / 256 / 1,000 queries of mixed lengths against
+// 200,000 words to 20 symbols, us: 141 / 719 / 1,681 with a launch per length
+// spread over the library's streams, 111 / 448 / 1,218 here.  (Ranges of 8: one
+// launch more for most batches, 4 queries of 600,000 words to 40 symbols 324
+// against 271; longer ranges cost the short rows the registers of the long.)
 //
 // k_merge_lists: one wavefront per row merges its P partial lists into the
 // final top-k (and optionally reports the key of a given rank);
@@ -36,101 +44,107 @@ struct QueryArgs {
     int gap;
     int lo;                 // lower score bound (key origin)
     int k;                  // list length, 1..64
-    int rpw;                // row pairs per workgroup
     int64_t per;            // column slots per split (multiple of 256)
     int nsplit;
     uint64_t *partial;      // [rows][nsplit][k]
 };
 
-// LDS: two profiles, then the wave lists of both rows of a pair (2 x 4 x k keys).
+// LDS: the profile, then the wave lists of both rows of the pair (2 x 4 x k keys).
 __host__ __device__ constexpr uint32_t query_lds_bytes(int LA, int alphabet, int k)
 {
-    return 2u * profile_bytes(LA, alphabet) + 2u * 4u * 8u * (uint32_t)k;
+    return profile_bytes(LA, alphabet) + 2u * 4u * 8u * (uint32_t)k;
 }
 
+// Row pair p of length LA.
 template <int LA>
-__global__ __launch_bounds__(kThreads) void k_query_tiled(QueryArgs Q)
+__device__ __forceinline__ void query_tile(const QueryArgs &Q, uint32_t p, uint8_t *lds)
 {
-    extern __shared__ __align__(16) uint8_t lds[];
-    const uint32_t off0 = Q.R.off[LA], off1 = Q.R.off[LA + 1];
-    const uint32_t pbeg = off0 + blockIdx.x * (uint32_t)Q.rpw;
-    if (pbeg >= off1) return;
-    const uint32_t pend = min(pbeg + (uint32_t)Q.rpw, off1);
     const int split = blockIdx.y;
     const int64_t c0 = (int64_t)split * Q.per;
     const int64_t c1 = min(c0 + Q.per, Q.C.nslots);
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    const uint32_t prof_bytes = profile_bytes(LA, Q.alphabet);
-    const ProfileRole role = profile_role(tid, Q.alphabet);
-    uint64_t *wl = reinterpret_cast<uint64_t *>(lds + 2 * prof_bytes);   // [2 rows][4 waves][k]
-
-    for (uint32_t p = pbeg; p < pend; ++p) {
-        const int32_t a0 = Q.R.pairs[2 * p], a1 = Q.R.pairs[2 * p + 1];
-        const uint8_t *prof = lds + (p & 1) * prof_bytes;
-        build_profile<LA>(Q.wtab, Q.alphabet, reinterpret_cast<uint32_t *>(lds + (p & 1) * prof_bytes),
-                          Q.R.sym + (int64_t)a0 * kWordBytes, Q.R.sym + (int64_t)(a1 >= 0 ? a1 : a0) * kWordBytes,
-                          role);
-        __syncthreads();
-        uint64_t list0 = 0, list1 = 0, thr0 = 0, thr1 = 0;
-        // the next step's column word is loaded while this step's DP and
-        // list offers run (a split is a few steps, so load latency would
-        // otherwise dominate a lightly loaded GPU)
-        int64_t base = c0 + wave * 64;
-        int lb_n = 0;
-        int32_t d_n = -1;
-        uint32_t bw_n[kWordBytes / 4];
-        if (base < c1) {
-            lb_n = Q.C.len[base + lane];
-            d_n = Q.C.orig[base + lane];
-            load_word(bw_n, Q.C.sym + (base + lane) * kWordBytes);
-        }
-        for (; base < c1; base += kThreads) {
-            const int lb = lb_n;
-            const int32_t d = d_n;
-            uint32_t bw[kWordBytes / 4];
-#pragma unroll
-            for (int q = 0; q < kWordBytes / 4; ++q) bw[q] = bw_n[q];
-            const int64_t nx = base + kThreads + lane;
-            if (base + kThreads < c1) {
-                lb_n = Q.C.len[nx];
-                d_n = Q.C.orig[nx];
-                load_word(bw_n, Q.C.sym + nx * kWordBytes);
-            }
-            const int lbmax_w = __builtin_amdgcn_readlane(lb, 63);
-            int s0, s1;
-            pair_scores_regs<LA>(bw, lb, lbmax_w, prof, Q.gap, s0, s1);
-            const uint64_t key0 = d >= 0 ? nb_key(s0, Q.lo, (uint32_t)d) : 0;
-            const uint64_t key1 = d >= 0 ? nb_key(s1, Q.lo, (uint32_t)d) : 0;
-            wl_offer(list0, thr0, key0, Q.k, lane);
-            if (a1 >= 0) wl_offer(list1, thr1, key1, Q.k, lane);
-        }
-        if (Q.nsplit == 1) {   // uniform: the wave lists are the row's partial lists
-            if (lane < Q.k) {
-                Q.partial[((int64_t)Q.R.orig[a0] * 4 + wave) * Q.k + lane] = list0;
-                if (a1 >= 0) Q.partial[((int64_t)Q.R.orig[a1] * 4 + wave) * Q.k + lane] = list1;
-            }
-            continue;
-        }
-        if (lane < Q.k) {
-            wl[(0 * 4 + wave) * Q.k + lane] = list0;
-            wl[(1 * 4 + wave) * Q.k + lane] = list1;
-        }
-        __syncthreads();
-        // wavefront h merges the four wave lists of row h of the pair
-        if (wave < 2 && (wave == 0 || a1 >= 0)) {
-            const uint64_t *src = wl + wave * 4 * Q.k;
-            uint64_t list = 0, t = 0;
-            for (int base = 0; base < 4 * Q.k; base += 64) {
-                const int i = base + lane;
-                wl_offer(list, t, i < 4 * Q.k ? src[i] : 0, Q.k, lane);
-            }
-            const int32_t row = Q.R.orig[wave == 0 ? a0 : a1];
-            if (lane < Q.k) Q.partial[((int64_t)row * Q.nsplit + split) * Q.k + lane] = list;
-        }
-        __syncthreads();   // the wave lists are rewritten by the next row pair
+    const int32_t a0 = Q.R.pairs[2 * p], a1 = Q.R.pairs[2 * p + 1];
+    build_profile<LA>(Q.wtab, Q.alphabet, reinterpret_cast<uint32_t *>(lds), Q.R.sym + (int64_t)a0 * kWordBytes,
+                      Q.R.sym + (int64_t)(a1 >= 0 ? a1 : a0) * kWordBytes, profile_role(tid, Q.alphabet));
+    __syncthreads();
+    uint64_t list0 = 0, list1 = 0, thr0 = 0, thr1 = 0;
+    // the next step's column word is loaded while this step's DP and
+    // list offers run (a split is a few steps, so load latency would
+    // otherwise dominate a lightly loaded GPU)
+    int64_t base = c0 + wave * 64;
+    int lb_n = 0;
+    int32_t d_n = -1;
+    uint32_t bw_n[kWordBytes / 4];
+    if (base < c1) {
+        lb_n = Q.C.len[base + lane];
+        d_n = Q.C.orig[base + lane];
+        load_word(bw_n, Q.C.sym + (base + lane) * kWordBytes);
     }
+    for (; base < c1; base += kThreads) {
+        const int lb = lb_n;
+        const int32_t d = d_n;
+        uint32_t bw[kWordBytes / 4];
+#pragma unroll
+        for (int q = 0; q < kWordBytes / 4; ++q) bw[q] = bw_n[q];
+        const int64_t nx = base + kThreads + lane;
+        if (base + kThreads < c1) {
+            lb_n = Q.C.len[nx];
+            d_n = Q.C.orig[nx];
+            load_word(bw_n, Q.C.sym + nx * kWordBytes);
+        }
+        const int lbmax_w = __builtin_amdgcn_readlane(lb, 63);
+        int s0, s1;
+        pair_scores_regs<LA>(bw, lb, lbmax_w, lds, Q.gap, s0, s1);
+        const uint64_t key0 = d >= 0 ? nb_key(s0, Q.lo, (uint32_t)d) : 0;
+        const uint64_t key1 = d >= 0 ? nb_key(s1, Q.lo, (uint32_t)d) : 0;
+        wl_offer(list0, thr0, key0, Q.k, lane);
+        if (a1 >= 0) wl_offer(list1, thr1, key1, Q.k, lane);
+    }
+    if (Q.nsplit == 1) {   // uniform: the wave lists are the row's partial lists
+        if (lane < Q.k) {
+            Q.partial[((int64_t)Q.R.orig[a0] * 4 + wave) * Q.k + lane] = list0;
+            if (a1 >= 0) Q.partial[((int64_t)Q.R.orig[a1] * 4 + wave) * Q.k + lane] = list1;
+        }
+        return;
+    }
+    uint64_t *wl = reinterpret_cast<uint64_t *>(lds + profile_bytes(LA, Q.alphabet));   // [2 rows][4 waves][k]
+    if (lane < Q.k) {
+        wl[(0 * 4 + wave) * Q.k + lane] = list0;
+        wl[(1 * 4 + wave) * Q.k + lane] = list1;
+    }
+    __syncthreads();
+    // wavefront h merges the four wave lists of row h of the pair
+    if (wave < 2 && (wave == 0 || a1 >= 0)) {
+        const uint64_t *src = wl + wave * 4 * Q.k;
+        uint64_t list = 0, t = 0;
+        for (int base2 = 0; base2 < 4 * Q.k; base2 += 64) {
+            const int i = base2 + lane;
+            wl_offer(list, t, i < 4 * Q.k ? src[i] : 0, Q.k, lane);
+        }
+        const int32_t row = Q.R.orig[wave == 0 ? a0 : a1];
+        if (lane < Q.k) Q.partial[((int64_t)row * Q.nsplit + split) * Q.k + lane] = list;
+    }
+}
+
+template <int LA, int HI>
+__device__ __forceinline__ void query_dispatch(const QueryArgs &Q, uint32_t p, uint8_t *lds)
+{
+    if constexpr (LA <= HI) {
+        if (p < Q.R.off[LA + 1])
+            query_tile<LA>(Q, p, lds);
+        else
+            query_dispatch<LA + 1, HI>(Q, p, lds);
+    }
+}
+
+// blockIdx.x = the row pair among those of lengths LO .. HI, blockIdx.y = the split.
+template <int LO, int HI>
+__global__ __launch_bounds__(kThreads) void k_query_class(QueryArgs Q)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    query_dispatch<LO, HI>(Q, Q.R.off[LO] + blockIdx.x, lds);
 }
 
 #ifdef NW_LAUNCH_TU   // non-template kernels: compiled in the launcher unit only

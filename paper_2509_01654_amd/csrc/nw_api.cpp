@@ -1166,9 +1166,9 @@ int nw_query(const nw_vocab *v, const uint8_t *h_q_symbols, const uint64_t *h_q_
     DevVocab Dq = D;
     Dq.lo = (int32_t)lo;
     uint64_t *partial = reinterpret_cast<uint64_t *>(ws + W.partial);
-    // queries of several lengths: their launches run side by side (256 queries
-    // of 200k words 1.36 -> 0.56 ms)
-    if ((e = launch_query(Dq, R, img.off.data(), full_colset(D), (int)k, W.nsplit, partial, st, n_q > 1)) != hipSuccess ||
+    // on the caller's stream alone: the library's streams may hold another
+    // caller's long pass
+    if ((e = launch_query(Dq, R, img.off.data(), full_colset(D), (int)k, W.nsplit, partial, st)) != hipSuccess ||
         (e = launch_merge(partial, query_lists(W.nsplit), (int)k, (int64_t)n_q, (int)k, (int)lo, d_score, d_index, nullptr, 1, st)) != hipSuccess)
         return dev_fail(e, "launching the query kernels");
     return ok();

@@ -13,6 +13,11 @@ namespace nw {
 #define NW_CLASS8 X(0, 7) X(8, 15) X(16, 23) X(24, 31) X(32, 39) X(40, 47) X(48, 48)
 constexpr int kNumClass8 = 7;
 
+// Ranges of row lengths of the query kernel, one translation unit each: kQuerySpan
+// lengths, the last one more.
+#define NW_QUERY X(0, 15) X(16, 31) X(32, 48)
+constexpr int kQuerySpan = 16, kNumQuery = 3;
+
 // Classes of four lengths of the bit-plane kernels, by translation unit.
 #define NW_BITS_SPLITS X(0, 1) X(2, 2) X(3, 3) X(4, 4) X(5, 5) X(6, 6) X(7, 7) X(8, 8) X(9, 9) X(10, 10) X(11, 11)
 
@@ -23,7 +28,6 @@ struct KernelTables {
     const void *tri[kMaxLen + 1];
     const void *tri_code1[kMaxLen + 1];  // the same with score codes and dword stores, one row pair a step
     const void *tri_code2[kMaxLen + 1];  // two row pairs a step (rows 1 .. 16; else NULL)
-    const void *query[kMaxLen + 1];
     const void *probe_thr[kMaxLen + 1];  // threshold pre-pass by selection
     const void *topk[kMaxLen + 1];
     const void *topk_code[kMaxLen + 1];  // the same with the score-code epilogue
@@ -36,6 +40,7 @@ struct KernelTables {
     const void *persist1[kMaxLen + 1];   // persistent batched kernel, one per row length
     const void *persist8[kNumClass8];    // persistent batched kernel, one per class of 8 lengths
     const void *class8[kNumClass8];      // small-dictionary triangle kernel, one per class of 8 lengths
+    const void *query[kNumQuery];        // queries, one per range of lengths
 };
 
 #define X(lo, hi) void nw_fill_##lo(KernelTables &t);
@@ -49,6 +54,9 @@ NW_BITS_SPLITS
 #undef X
 #define X(lo, hi) void nw_fill_class_##lo(KernelTables &t);
 NW_CLASS8
+#undef X
+#define X(lo, hi) void nw_fill_query_##lo(KernelTables &t);
+NW_QUERY
 #undef X
 
 const KernelTables &kernel_tables();

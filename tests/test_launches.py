@@ -198,3 +198,21 @@ def check_column_layout(R):
 def test_column_layout_of_the_largest_dictionaries(recorder_library):
     """A grid holds fewer than 2^32 threads: the layout of 357 million words and more goes in several launches."""
     _child(recorder_library, "check_column_layout")
+
+
+def check_query_stream(R):
+    h = R.load(*words(20000, 40, 1, 32), R.nw.Scoring(40, 1, -1, -1))
+    P, stream = R.P, 0x7770
+    for n in (1, 2, 64, 300, 1000):   # the largest goes up by a copy, the others as kernel arguments
+        qs, qo = words(n, 40, 0, 40, seed=n)
+        qs = np.ascontiguousarray(qs, dtype=np.uint8)
+        out = R.launches(R.lib.nw_query, h, qs.ctypes.data, qo.ctypes.data, n, 16, P(1 << 41), P(1 << 42), P(1 << 43),
+                         1 << 40, P(stream))
+        assert any("k_query" in x[0] for x in out)
+        assert {x[4] for x in out} == {stream}, (n, out)
+        assert sum(x[1][0] for x in out if "k_query" in x[0]) >= (n + 1) // 2   # every row pair
+
+
+def test_queries_run_on_the_callers_stream(recorder_library):
+    """A query waits for no other caller's work: nothing of it goes to the library's streams."""
+    _child(recorder_library, "check_query_stream")
