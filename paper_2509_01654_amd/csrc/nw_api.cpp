@@ -464,8 +464,11 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     int bits = 0;
     if (max_len <= (uint32_t)kMaxLen && symmetric && wmax <= 7 && sc->gap >= -7) {
         bool plain = sc->gap >= -3;
-        for (int x = 0; x < A && plain; ++x)
-            for (int y = 0; y < A && plain; ++y) plain = sim[(size_t)x * A + y] - 2 * sc->gap == (x == y ? 3 : 1);
+        if (!sc->submat)
+            plain = plain && sc->match - 2 * sc->gap == 3 && (A == 1 || sc->mismatch - 2 * sc->gap == 1);
+        else
+            for (int x = 0; x < A && plain; ++x)
+                for (int y = 0; y < A && plain; ++y) plain = sim[(size_t)x * A + y] - 2 * sc->gap == (x == y ? 3 : 1);
         bits = plain ? 2 : 3;
     }
 
@@ -478,8 +481,8 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     if (int rc = refuse_capture((hipStream_t)hip_stream, "nw_load_vocab")) return rc;
 
     // host image of the device layout
-    const bool narrow = max_len <= (uint32_t)kMaxLen;
-    const uint64_t img_bytes = narrow ? L.ccol : L.total;
+    // (the plane kernels' arrays, the last, only where they run)
+    const uint64_t img_bytes = bits ? L.ccol : L.rg_off;
     std::vector<uint8_t> img(img_bytes, 0);
     // lane words are padded with the sentinel symbol (= alphabet)
     std::memset(img.data() + L.bsym, A, (size_t)L.nb * L.CB * L.WB);
@@ -608,7 +611,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     }
     // groups of 32 slots by their longest word (the last: slots are length-sorted)
     std::vector<uint32_t> h_bitlens(kMaxLen / 4, 0);
-    if (narrow) {
+    if (bits) {
         uint32_t *rg_off = reinterpret_cast<uint32_t *>(img.data() + L.rg_off);
         const uint32_t per = (uint32_t)L.CB / 32;
         for (int blk = 0; blk < L.nb; ++blk) {
@@ -624,7 +627,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
         }
         rg_off[(size_t)L.nb * (LM + 1)] = (uint32_t)L.nb * per;
         if (L.TW != L.CB) {
-            // windows: the slots of their block in order, padding first
+            // windows of kTriWindow or fewer words: their slots in order, padding first
             uint8_t *tlen = img.data() + L.tlen;
             uint16_t *tcol = reinterpret_cast<uint16_t *>(img.data() + L.tcol);
             std::vector<uint64_t> next(L.nwin);
@@ -635,27 +638,42 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
                     tcol[next[w]++] = 0xFFFF;
                 }
             }
-            // a window of several blocks takes their slots sorted by length
-            // again (a counting sort; within a length in slot order)
-            std::vector<uint32_t> order((size_t)L.nb * L.CB), at(LM + 2);
-            if (L.TW > L.CB)
+            if (L.TW < L.CB) {   // a block's slots, dealt to its windows
+                for (int blk = 0; blk < L.nb; ++blk) {
+                    uint64_t *to = &next[(size_t)blk * (L.CB / L.TW)];
+                    for (size_t s = (size_t)blk * L.CB; s < (size_t)(blk + 1) * L.CB; ++s) {
+                        const unsigned col = bcol[s];
+                        if (col == 0xFFFF) continue;
+                        const uint64_t at = to[col / kTriWindow]++;
+                        tlen[at] = blen[s];
+                        tcol[at] = (uint16_t)(col % kTriWindow);
+                    }
+                }
+            } else {
+                // a window of several blocks takes their slots sorted by length
+                // again (a counting sort; within a length in slot order)
+                std::vector<uint32_t> order((size_t)L.nb * L.CB), at(LM + 2);
                 for (size_t s = 0; s < order.size(); ++s) ++at[blen[s] + 1];
-            std::partial_sum(at.begin(), at.end(), at.begin());
-            for (size_t s = 0; s < order.size(); ++s) order[L.TW > L.CB ? at[blen[s]]++ : s] = (uint32_t)s;
-            for (const uint32_t s : order) {
-                if (borig[s] < 0) continue;
-                const int w = borig[s] / L.TW;
-                tlen[next[w]] = blen[s];
-                tcol[next[w]++] = (uint16_t)(borig[s] - w * L.TW);
+                std::partial_sum(at.begin(), at.end(), at.begin());
+                for (size_t s = 0; s < order.size(); ++s) order[at[blen[s]]++] = (uint32_t)s;
+                for (const uint32_t s : order) {
+                    if (borig[s] < 0) continue;
+                    const int w = borig[s] / L.TW;
+                    tlen[next[w]] = blen[s];
+                    tcol[next[w]++] = (uint16_t)(borig[s] - w * L.TW);
+                }
             }
         }
+    }
+    if (bits == 3) {   // two planes look for equal symbols
         uint32_t *wplanes = reinterpret_cast<uint32_t *>(img.data() + L.wplanes);
-        for (int x = 0; x < A; ++x)
+        for (int x = 0; x < A; ++x) {
+            uint32_t *of = wplanes + (size_t)x * 3 * 8;
             for (int y = 0; y < A; ++y) {
-                const int w = std::min(std::max(sim[(size_t)x * A + y] - 2 * sc->gap, 0), 7);
-                for (int q = 0; q < 3; ++q)
-                    if (w >> q & 1) wplanes[((size_t)x * 3 + q) * 8 + y / 32] |= 1u << (y % 32);
+                const uint32_t w = (uint32_t)std::min(std::max(sim[(size_t)x * A + y] - 2 * sc->gap, 0), 7);
+                for (int q = 0; q < 3; ++q) of[q * 8 + y / 32] |= (w >> q & 1u) << (y % 32);
             }
+        }
     }
     for (int x = 0; x < A; ++x)
         for (int y = 0; y < A; ++y) {
@@ -713,7 +731,7 @@ int nw_load_vocab(const uint8_t *h_symbols, const uint64_t *h_offsets, uint64_t 
     D.tlen = windows ? base + L.tlen : D.blen;
     D.tcol = windows ? reinterpret_cast<const uint16_t *>(base + L.tcol) : D.bcol;
     D.tccol = windows ? reinterpret_cast<const uint32_t *>(base + L.tccol) : D.ccol;
-    if (narrow) {
+    if (bits) {
         e = launch_column_layout(D, D.blen, D.bcol, D.CB, (int64_t)L.nb * L.CB, reinterpret_cast<uint32_t *>(base + L.ccol), st);
         if (e == hipSuccess && windows)
             e = launch_column_layout(D, D.tlen, D.tcol, D.TW, (int64_t)L.nwin * L.TW,

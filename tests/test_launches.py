@@ -216,3 +216,15 @@ def check_query_stream(R):
 def test_queries_run_on_the_callers_stream(recorder_library):
     """A query waits for no other caller's work: nothing of it goes to the library's streams."""
     _child(recorder_library, "check_query_stream")
+
+
+def check_load(R):
+    for sc, lmax, planes in ((PLAIN, 20, True), (MATRIX, 20, True), ((4, -1, -2), 20, False), (PLAIN, 49, False)):
+        R.hip.rec_clear()
+        R.load(*words(3000, 40, lmax, lmax), R.nw.Scoring(40, *sc))
+        names = [R.hip.rec_get(i).contents.name.decode() for i in range(R.hip.rec_count())]
+        assert any("k_column_layout" in x for x in names) == planes, (sc, lmax, names)
+
+
+def test_load_lays_out_planes_only_where_they_run(recorder_library):
+    _child(recorder_library, "check_load")
