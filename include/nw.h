@@ -439,10 +439,10 @@ int nw_batch_info(const nw_batch *b, uint64_t *items, uint32_t *launches);
 
 void nw_batch_destroy(nw_batch *b);
 
-/* Choose nw_batch_options for this batch by timing candidates on it
- * (the tiled form launched eagerly, then a coordinate search over class
- * width, workgroups per CU and pairs per item with graphs;
- * the workspace must hold the largest candidate plan, see
+/* Choose nw_batch_options for this batch by timing candidates on it (a
+ * coordinate search over class width, workgroups per CU and pairs per item, every
+ * candidate launched eagerly; use_graph is 1 in a persistent choice, 0 in the
+ * tiled one; the workspace must hold the largest candidate plan, see
  * nw_batch_workspace_bytes with pairs_per_item = 16).  With cache_path, a
  * result cached for the same device and workload signature is returned
  * without timing, and new results are appended (one JSON object per line).

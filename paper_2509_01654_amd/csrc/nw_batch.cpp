@@ -14,8 +14,11 @@
 // (library streams when eager, chains of kernel nodes inside the capture).
 //
 // Autotuner: times candidate (class width, workgroups per CU, pairs per item)
-// settings on the batch itself and caches the best per device and workload
-// signature in a JSON-lines file.
+// settings on the batch itself, launched eagerly, and caches the best per device
+// and workload signature in a JSON-lines file.  It builds no graph: a process that
+// created, replayed and destroyed one per candidate, each destroyed as soon as its
+// last replay had completed, has ended with a segmentation fault in a thread of
+// the HIP runtime, the cause not known.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -393,21 +396,10 @@ int nw_batch_autotune(const nw_vocab *const *v, uint32_t nv, void *const *d_outs
         return rc;
     };
     // coordinate search from (width 8, 4 workgroups per CU, 64 pairs per item)
-    nw_batch_options cur{8, 4, 64, 1};
+    nw_batch_options cur{8, 4, 64, 0};
     float cur_ms = 0;
     int rc = time_one(cur, cur_ms);
     const uint32_t widths[] = {0, 1, 8}, wgs[] = {2, 4, 8}, ppi[] = {16, 64, 0};
-    // the tiled form launched eagerly (its launches overlap on forked
-    // library streams; the captured form replays the same chains as a graph)
-    if (!rc) {
-        const nw_batch_options o{0, 1, 0, 0};
-        float ms = 0;
-        rc = time_one(o, ms);
-        if (!rc && ms < cur_ms) {
-            cur = o;
-            cur_ms = ms;
-        }
-    }
     for (int dim = 0; dim < 3 && !rc; ++dim) {
         if (dim > 0 && cur.class_width == 0) break;   // the tiled form has no persistent parameters
         const uint32_t *vals = dim == 0 ? widths : dim == 1 ? wgs : ppi;
@@ -431,6 +423,9 @@ int nw_batch_autotune(const nw_vocab *const *v, uint32_t nv, void *const *d_outs
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     if (rc) return rc;
+    // one graph for the plan that is kept: the persistent form's many launches are
+    // replayed, the tiled form's few go out as they were timed
+    cur.use_graph = cur.class_width != 0;
     *best = cur;
     if (best_ms) *best_ms = cur_ms;
     if (cache_path) {

@@ -64,6 +64,7 @@ int hipEventSynchronize(ptr e) { (void)e; return 0; }
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int d) { (void)d; return 0; }
+int hipGetDevicePropertiesR0600(char *p, int d) { (void)d; memset(p, 0, 1472); strcpy(p, "recorder"); return 0; }
 int hipGetLastError(void)
 {
     const int e = last_error;
