@@ -444,8 +444,8 @@ void nw_batch_destroy(nw_batch *b);
  * candidate launched eagerly; use_graph is 1 in a persistent choice, 0 in the
  * tiled one; the workspace must hold the largest candidate plan, see
  * nw_batch_workspace_bytes with pairs_per_item = 16).  With cache_path, a
- * result cached for the same device and workload signature is returned
- * without timing, and new results are appended (one JSON object per line).
+ * result cached by the same kernels for the same device and workload signature
+ * (sizes and scoring) is returned without timing, and new results are appended (one JSON object per line).
  * Overwrites the outputs. */
 int nw_batch_autotune(const nw_vocab *const *v, uint32_t nv, void *const *d_outs, nw_dtype dt, void *d_ws,
                       uint64_t ws_bytes, void *hip_stream, const char *cache_path, nw_batch_options *best,

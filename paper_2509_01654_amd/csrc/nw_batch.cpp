@@ -341,13 +341,18 @@ int nw_batch_autotune(const nw_vocab *const *v, uint32_t nv, void *const *d_outs
                       float *best_ms)
 {
     if (!v || !nv || !best) return fail(NW_EINVAL, "NULL argument");
-    // workload signature: device, dtype, and per dictionary n, longest word, alphabet, symbols
+    // workload signature: device, dtype, the kernels' generation (raised when a
+    // form's kernels change, so that times taken with others no longer answer),
+    // and per dictionary n, longest word, alphabet, symbols and what its scoring
+    // means for the kernels: planes of a difference, score bounds
+    constexpr int kKernels = 2;
     std::ostringstream key;
-    key << device_name(v[0]->device) << "|dt" << (int)dt;
+    key << device_name(v[0]->device) << "|dt" << (int)dt << "|k" << kKernels;
     for (uint32_t i = 0; i < nv; ++i) {
         uint64_t sl = 0;
         for (uint8_t l : v[i]->h_clen) sl += l;
-        key << "|" << v[i]->n << ":" << v[i]->max_len << ":" << v[i]->dev.alphabet << ":" << sl;
+        key << "|" << v[i]->n << ":" << v[i]->max_len << ":" << v[i]->dev.alphabet << ":" << sl << ":" << v[i]->dev.bits << ":"
+            << v[i]->lo << ":" << v[i]->hi;
     }
     const std::string k = key.str();
     if (cache_path) {

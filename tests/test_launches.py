@@ -230,22 +230,6 @@ def test_load_lays_out_planes_only_where_they_run(recorder_library):
     _child(recorder_library, "check_load")
 
 
-def check_packed_routes(R):
-    # the scorings of the GPU tests of the packed kernels do take them
-    h = R.load(*words(17000, 40, 0, 20), R.nw.Scoring(40, 4, -1, -2))
-    n, P = 17000, R.P
-    tri = {x[0] for x in _triangle(R, h, 0, n * (n - 1) // 2)}
-    assert all("k_tri_code" in x for x in tri) and any("Li1E" in x for x in tri) and any("Li2E" in x for x in tri), tri
-    assert all("k_edges_tiled" in x[0] for x in _edges(R, h, 0, 5000) if "k_edges" in x[0])
-    top = [x[0] for x in R.launches(R.lib.nw_all_pairs_topk_async, h, 16, P(1 << 41), P(1 << 42), P(1 << 44), P(1 << 43),
-                                    _topk_bytes(R, h, 16), None)]
-    assert any("k_topk_code" in x for x in top) and not any("bits" in x for x in top), top
-
-
-def test_packed_scorings_take_the_packed_kernels(recorder_library):
-    _child(recorder_library, "check_packed_routes")
-
-
 def _autotune(R, scoring, cache):
     hs = [R.load(*words(n, 20, 0, lmax, seed=n), R.nw.Scoring(20, *scoring)) for n, lmax in ((300, 10), (900, 16))]
     vh = (ctypes.c_void_p * 2)(*[h.value for h in hs])
@@ -264,11 +248,21 @@ def check_autotune(R):
     # (the recorder has no graphs: a candidate that captured one would fail here)
     with tempfile.TemporaryDirectory() as d:
         cache = d + "/tune.jsonl"
-        lines, first, _ = _autotune(R, PLAIN, cache)
-        assert len(lines) == 1
-        lines, again, _ = _autotune(R, PLAIN, cache)
-        assert len(lines) == 1 and bytes(first) == bytes(again) and first.use_graph == (first.class_width != 0)
+        for n, sc in enumerate([PLAIN, MATRIX, (4, -1, -2), (8, -1, -2)]):
+            lines, first, _ = _autotune(R, sc, cache)
+            assert len(lines) == n + 1, "another scoring's line answered"
+            lines, again, _ = _autotune(R, sc, cache)
+            assert len(lines) == n + 1, "its own line did not"
+            assert bytes(first) == bytes(again) and first.use_graph == (first.class_width != 0)
+        # a line without the kernels' generation and the scorings, as it was written before
+        old = d + "/old.jsonl"
+        with open(old, "w") as f:
+            lens = [np.diff(words(n, 20, 0, lmax, seed=n)[1].astype(np.int64)) for n, lmax in ((300, 10), (900, 16))]
+            key = "recorder/|dt2" + "".join(f"|{l.size}:{l.max()}:20:{l.sum()}" for l in lens)
+            f.write('{"key": "%s", "class_width": 1, "wg_per_cu": 2, "pairs_per_item": 16, "use_graph": 1, "ms": 0.001}\n' % key)
+        lines, best, ms = _autotune(R, PLAIN, old)
+        assert len(lines) == 2 and ms > 0.5, "a line of earlier kernels answered"
 
 
-def test_autotune_builds_no_graphs(recorder_library):
+def test_autotune_cache_tells_scorings_and_kernels_apart(recorder_library):
     _child(recorder_library, "check_autotune")
