@@ -266,3 +266,19 @@ def check_autotune(R):
 
 def test_autotune_cache_tells_scorings_and_kernels_apart(recorder_library):
     _child(recorder_library, "check_autotune")
+
+
+def check_packed_routes(R):
+    # the scorings of the GPU tests of the packed kernels do take them
+    h = R.load(*words(17000, 40, 0, 20), R.nw.Scoring(40, 4, -1, -2))
+    n, P = 17000, R.P
+    tri = {x[0] for x in _triangle(R, h, 0, n * (n - 1) // 2)}
+    assert all("k_tri_code" in x for x in tri) and any("Li1E" in x for x in tri) and any("Li2E" in x for x in tri), tri
+    assert all("k_edges_tiled" in x[0] for x in _edges(R, h, 0, 5000) if "k_edges" in x[0])
+    top = [x[0] for x in R.launches(R.lib.nw_all_pairs_topk_async, h, 16, P(1 << 41), P(1 << 42), P(1 << 44), P(1 << 43),
+                                    _topk_bytes(R, h, 16), None)]
+    assert any("k_topk_code" in x for x in top) and not any("bits" in x for x in top), top
+
+
+def test_packed_scorings_take_the_packed_kernels(recorder_library):
+    _child(recorder_library, "check_packed_routes")
