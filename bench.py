@@ -37,16 +37,15 @@ METRIC = "all-pairs NW GCUPS + pairs/s at 600k words; served query p50/p99 laten
 PEAK_ISSUE_CELLS = 256 * 64 * 2.4e9
 # The roofline of the bit-plane kernels (csrc/nw_bits.h): a cell of 32 pairs
 # takes 7 three-input functions where every match weighs 3 and every mismatch
-# 1 (two planes), and 22 with three planes.  v_bitop3_b32 in independent chains
-# on every CU sustains 56.4e12 lane-instructions/s on this card (measured; more
-# than the 39.3e12 of the packed unit), which over the functions is the ceiling.
-BIT_FUNCTION_RATE = 56.4e12
+# 1 (two planes), and 22 with three planes.  The rate at which the card issues
+# them (v_bitop3_b32, more than the packed unit's) is measured in the same run
+# (nw_function_issue_rate); over the functions of a cell it is the ceiling.
 BIT_FUNCTIONS = {2: 7, 3: 22}
 
 
-def bit_peak(planes: int) -> float:
-    """Cells per second of the bit-plane DP at the function issue ceiling."""
-    return 32 * BIT_FUNCTION_RATE / BIT_FUNCTIONS[planes]
+def bit_planes(planes: int) -> int:
+    """Planes the kernels of a workload hold: none where NW_DP=packed keeps the packed ones."""
+    return 0 if os.environ.get("NW_DP") == "packed" else planes
 
 
 # The algorithmic operation count of a cell (2 adds, 2 maxes, 1 similarity
@@ -59,11 +58,13 @@ OPS_PER_CELL = 5
 PEAK_16BIT_OPS = 256 * 64 * 2 * 2.4e9
 
 
-def roofline(cells: float, seconds: float, kernel: str, traffic=None, algorithmic_bytes=None, planes=0) -> dict:
+def roofline(cells: float, seconds: float, kernel: str, traffic=None, algorithmic_bytes=None, planes=0,
+             function_rate=None) -> dict:
     """The roofline record of a DP kernel pass that updates `cells` cells in
-    `seconds`; planes: 2 or 3 for the bit-plane kernels, 0 for the packed ones."""
+    `seconds`; planes: 2 or 3 for the bit-plane kernels (function_rate: their
+    functions per second as measured), 0 for the packed ones."""
     rate = cells / seconds
-    peak = bit_peak(planes) if planes else PEAK_ISSUE_CELLS
+    peak = 32 * function_rate / BIT_FUNCTIONS[planes] if planes else PEAK_ISSUE_CELLS
     rec = {"bound": "alu", "achieved": round(rate / 1e12, 3), "peak": round(peak / 1e12, 3),
            "unit": "10^12 DP cells/s (VALU issue ceiling: " +
                    (f"{BIT_FUNCTIONS[planes]} functions per 32 cells)" if planes else "one packed lane-instruction per cell)"),
@@ -127,17 +128,18 @@ def counter_traffic(path=None, sources=None):
     return float(fields["fetch_bytes"]), float(fields["write_bytes"])
 
 
-def measured_packed_peak(nw, torch, blocks=2048, trips=4096, runs=3):
-    """The packed lane-instruction rate the chip sustains during this run:
-    nw_packed_issue_rate's launch (the DP's add + max3 pair, independent
-    chains, every CU at full occupancy) timed with events on the current
-    stream; the best of `runs` after one warm-up launch."""
-    nw.packed_issue_rate(blocks, trips)
+def measured_rate(issue, torch, blocks=2048, trips=4096, runs=3):
+    """The lane-instruction rate the chip sustains during this run: the launch of
+    nw.packed_issue_rate (the packed DP's add + max3 pair) or
+    nw.function_issue_rate (the bit planes' function), independent chains, every
+    CU at full occupancy, timed with events on the current stream; the best of
+    `runs` after one warm-up launch."""
+    issue(blocks, trips)
     best = 0.0
     for _ in range(runs):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
-        n_instr = nw.packed_issue_rate(blocks, trips)
+        n_instr = issue(blocks, trips)
         e1.record()
         torch.cuda.synchronize()
         best = max(best, n_instr / (e0.elapsed_time(e1) / 1e3))
@@ -293,10 +295,11 @@ def bench_batched(args, nw, synth, torch, dev):
                    "pairs": pairs, "cells": cells, "options": b.options, "items": items, "launches": launches,
                    "autotune_s": round(tune_s, 1)},
         "roofline": roofline(cells, ms / 1e3,
-                             ("k_tri_bits (every dictionary's launches"
+                             (("k_tri_bits" if bit_planes(3) else "k_tri_code") + " (every dictionary's launches"
                               + (", graph replay)" if b.options["use_graph"] else ", eager on forked streams)")
                               if b.options["class_width"] == 0 else "k_tri_persist (graph replay)"),
-                             planes=3 if b.options["class_width"] == 0 else 0),
+                             planes=bit_planes(3) if b.options["class_width"] == 0 else 0,
+                             function_rate=measured_rate(nw.function_issue_rate, torch)),
         "output_GB_per_s": round(2 * pairs / (ms / 1e3) / 1e9, 1),
         "plain_per_dictionary_ms": round(plain_ms, 3),
         "plain_gcups": round(cells / (plain_ms / 1e3) / 1e9, 1),
@@ -373,7 +376,8 @@ def bench_edges(args, nw, synth, torch, dev):
                                    "clip(Poisson 8, 1, 32), +1/-1, gap -1)", "n_words": dv.n, "pairs": E,
                        "cells": cells, "edges": total},
             "edges_per_s": total / (ms / 1e3), "edge_bytes_per_s": 10 * total / (ms / 1e3),
-            "roofline": roofline(cells, ms / 1e3, "k_edges_bits (every LA)", planes=2)}
+            "roofline": roofline(cells, ms / 1e3, "k_edges_bits (every LA)" if bit_planes(2) else "k_edges_tiled (every LA)",
+                                 planes=bit_planes(2), function_rate=measured_rate(nw.function_issue_rate, torch))}
 
 
 def bench_export(args, nw, synth, torch, dev):
@@ -529,9 +533,16 @@ def main():
         # algorithmic bytes of the main pass: the words read once (48-byte
         # slots) and every word's top-k list written once (int16 + int32)
         alg_bytes = dv.n * 48 + dv.n * k * 6
-        rec["roofline"] = roofline(cells, main_ms / 1e3, "k_topk_bits (all-pairs main pass, every class)",
-                                   None if tr is None else tr[0] + tr[1], alg_bytes, planes=2)
-        rate = measured_packed_peak(nw, torch)
+        function_rate = measured_rate(nw.function_issue_rate, torch)
+        rec["roofline"] = roofline(cells, main_ms / 1e3,
+                                   "k_topk_bits (all-pairs main pass, every class)" if bit_planes(2)
+                                   else "k_topk_code (all-pairs main pass, every length)",
+                                   None if tr is None else tr[0] + tr[1], alg_bytes, planes=bit_planes(2),
+                                   function_rate=function_rate)
+        rec["roofline"]["function_peak"] = {
+            "kernel": "k_function_rate (nw_function_issue_rate: the bit planes' function, independent chains)",
+            "lane_functions_per_s": round(function_rate / 1e12, 3), "unit": "10^12 lane-functions per s"}
+        rate = measured_rate(nw.packed_issue_rate, torch)
         rec["roofline"]["packed_peak"] = {
             "kernel": "k_packed_rate (nw_packed_issue_rate: the packed DP's add + max3, independent chains)",
             "cells_per_s": round(rate / 1e12, 3), "unit": "10^12 packed lane-instructions (= cells of the packed DP) per s",
@@ -560,8 +571,9 @@ def main():
                                      "+1/-1, gap -1)", "n_words": dv.n, "pairs": E, "cells": cells}
         tr = counter_traffic(TRI_COUNTER_SUMMARY, TRI_SOURCES) if args.workload == "mid" else None
         # algorithmic bytes: one int8 score written per pair, the words read once
-        rec["roofline"] = roofline(cells, ms_per_step / 1e3, "k_tri_bits (every LA)",
-                                   None if tr is None else tr[0] + tr[1], E + dv.n * 48, planes=2)
+        rec["roofline"] = roofline(cells, ms_per_step / 1e3, "k_tri_bits (every LA)" if bit_planes(2) else "k_tri_code",
+                                   None if tr is None else tr[0] + tr[1], E + dv.n * 48, planes=bit_planes(2),
+                                   function_rate=measured_rate(nw.function_issue_rate, torch))
         if tr is not None:
             # algorithmic bytes: one int8 score written per pair; the words read are ~1 MB
             rec["roofline"]["traffic_detail"] = {

@@ -495,6 +495,11 @@ int nw_ego_network(uint64_t n, const int64_t *d_row_ptr, const int32_t *d_adj, c
  * (blocks or trips 0, NULL out), NW_EDEVICE. */
 int nw_packed_issue_rate(uint32_t blocks, uint32_t trips, uint64_t *lane_instructions, void *hip_stream);
 
+/* The same for the three-input boolean function of 32 bits that the bit-plane
+ * kernels are made of (7 per cell of 32 pairs with two planes, 22 with three):
+ * trips x 64 of them per thread.  Same arguments and errors. */
+int nw_function_issue_rate(uint32_t blocks, uint32_t trips, uint64_t *lane_instructions, void *hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

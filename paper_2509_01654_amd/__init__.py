@@ -91,6 +91,7 @@ def load_library(path: str = LIB_PATH):
         "nw_export_triangle": (ctypes.c_int, [P, u64, u64, ctypes.c_int, u64, P, P, _CHUNK_FN, P, P]),
         "nw_graph_workspace_bytes": (ctypes.c_int, [u64, ctypes.POINTER(u64)]),
         "nw_packed_issue_rate": (ctypes.c_int, [u32, u32, ctypes.POINTER(u64), P]),
+        "nw_function_issue_rate": (ctypes.c_int, [u32, u32, ctypes.POINTER(u64), P]),
         "nw_graph_csr": (ctypes.c_int, [u64, P, P, u64, P, P, P, u64, P]),
         "nw_ego_network": (ctypes.c_int, [u64, P, P, P, u32, u32, P, P]),
     }
@@ -171,6 +172,14 @@ def packed_issue_rate(blocks: int, trips: int, stream=None) -> int:
     lib = load_library()
     out = ctypes.c_uint64()
     _check(lib.nw_packed_issue_rate(blocks, trips, ctypes.byref(out), _stream_handle(stream)))
+    return out.value
+
+
+def function_issue_rate(blocks: int, trips: int, stream=None) -> int:
+    """The same for the boolean function of the bit-plane kernels."""
+    lib = load_library()
+    out = ctypes.c_uint64()
+    _check(lib.nw_function_issue_rate(blocks, trips, ctypes.byref(out), _stream_handle(stream)))
     return out.value
 
 
