@@ -129,13 +129,13 @@ __device__ __forceinline__ void query_tile(const QueryArgs &Q, uint32_t p, uint8
 }
 
 template <int LA, int HI>
-__device__ __forceinline__ void query_dispatch(const QueryArgs &Q, uint32_t p, uint8_t *lds)
+__device__ __forceinline__ void query_dispatch(const QueryArgs &Q, int la, uint32_t p, uint8_t *lds)
 {
     if constexpr (LA <= HI) {
-        if (p < Q.R.off[LA + 1])
+        if (la == LA)
             query_tile<LA>(Q, p, lds);
         else
-            query_dispatch<LA + 1, HI>(Q, p, lds);
+            query_dispatch<LA + 1, HI>(Q, la, p, lds);
     }
 }
 
@@ -144,7 +144,15 @@ template <int LO, int HI>
 __global__ __launch_bounds__(kThreads) void k_query_class(QueryArgs Q)
 {
     extern __shared__ __align__(16) uint8_t lds[];
-    query_dispatch<LO, HI>(Q, Q.R.off[LO] + blockIdx.x, lds);
+    // the offsets are loaded together: testing one after the other chains their loads
+    uint32_t off[HI - LO + 2];
+#pragma unroll
+    for (int l = 0; l <= HI - LO + 1; ++l) off[l] = Q.R.off[LO + l];
+    const uint32_t p = off[0] + blockIdx.x;
+    int la = LO;
+#pragma unroll
+    for (int l = 1; l <= HI - LO + 1; ++l) la += p >= off[l] ? 1 : 0;
+    query_dispatch<LO, HI>(Q, la, p, lds);
 }
 
 #ifdef NW_LAUNCH_TU   // non-template kernels: compiled in the launcher unit only
