@@ -15,9 +15,10 @@
 // to 16 symbols under a matrix, a fifth of the pairs pass: 9.7 ms packed, 5.9 ms
 // with 64 at a time, 2.2 ms), and in a tile cut by the range the rows outside it
 // are left out before the DP (333 rows of 600,000 words, 28 million edges: 18.1
-// ms packed, 39.6 ms with the range tested at the queue, 6.7 ms).  100,000 words
-// of up to 32 symbols, the normalised slice [60, 100], its graph and an ego
-// network: 13.5 ms with the packed DP (k_edges_tiled), 2.4 ms here.
+// ms packed, 39.6 ms with the range tested at the queue, 6.7 ms).  Where hardly a
+// pair passes, the longer drain and the mask cost 2 %: 100,000 words of up to 32
+// symbols, the normalised slice [60, 100], 2.11 ms with 64 at a time, 2.16 here (with
+// its graph and an ego network 13.7 ms packed, 2.5 ms).
 #pragma once
 
 #include "k_edges.h"

@@ -322,7 +322,7 @@ __device__ __forceinline__ void tri_bits_tile(const DevVocab &V, uint32_t r, uin
                 }
             }
             __syncthreads();
-            // the row segments: a wavefront takes every fourth staging row, a
+            // the row segments: a wavefront takes every NWAVE-th staging row, a
             // lane eight columns of it at a time
             const TriRow *info = reinterpret_cast<const TriRow *>(lds + gb + bit_group_bytes(LA, S::kTab, A));
             for (int j = wave; j < (int)SJ; j += NWAVE) {

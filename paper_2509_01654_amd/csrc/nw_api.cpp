@@ -67,7 +67,9 @@ int refuse_capture(hipStream_t stream, const char *call)
 // batched workload's 40k..100k-word dictionaries of words up to 31..48
 // symbols 7 % slower).  Past 131k words, blocks of 3072: the 600k-word top-k
 // main pass took 420 ms with 2048, 413 with 2560, 407 with 3072, 410 with
-// 3584 and 417 with 4096 (the 50k-word triangle is slower with 3072).
+// 3584 and 417 with 4096 (the 50k-word triangle is slower with 3072).  All of
+// these are the packed kernels' times; the plane kernels run in the same blocks
+// and were not timed with others.
 int choose_block(uint64_t n, uint32_t max_len)
 {
     if (n <= 16384) return 256;

@@ -15,9 +15,7 @@
 // A cell of 32 pairs is then a small network of three-input boolean functions
 // (v_bitop3_b32), one vector instruction per function and 32 pairs:
 //     Bits2  (match weight 3, every mismatch weight 1: +1 / -1 / gap -1 and
-//            whatever shifts to it): 2 planes, 7 functions per cell, the
-//            fewest a search over all networks of that form found (none with
-//            6 exists under any two-bit code of the differences);
+//            whatever shifts to it): 2 planes, 7 functions per cell;
 //     Bits3  (any similarity with w <= 7): 3 planes, 22 functions per cell.
 // The packed binary16 form of nw_dp.h issues 32 lane-instructions for the
 // same 32 cells, at about two thirds of the rate: on MI355X v_bitop3_b32 was

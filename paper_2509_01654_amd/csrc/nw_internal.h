@@ -179,9 +179,9 @@ __host__ __device__ constexpr int query_lists(int nsplit) { return nsplit == 1 ?
 
 // Per-row top-k lists of the rows R (pairs grouped by length, h_off = host
 // copy of R.off) against the column set C, split over nsplit column ranges:
-// partial[row][query_lists(nsplit)][k].  Scoring from V.  fork_streams spreads the
-// per-length launches over library streams (throughput calls; latency-bound
-// callers such as the server keep them on `stream`).
+// partial[row][query_lists(nsplit)][k].  Scoring from V.  A launch per range of
+// lengths; fork_streams spreads them over library streams (the threshold pre-pass;
+// queries and the server keep them on `stream`).
 hipError_t launch_query(const DevVocab &V, const RowSet &R, const uint32_t *h_off, const ColSet &C, int k,
                         int nsplit, uint64_t *partial, hipStream_t stream, bool fork_streams = false);
 
